@@ -12,24 +12,32 @@ namespace {
 struct ConvConfig {
     const char* name;  // "TMxTNxBK"
     int tm, tn, bk, threads;
+    bool direct;
     LaunchFn launch;
 };
 
 #define CNN_CONV_ENTRY(I, WMW, WNW, FM, FN, BK, KS, ST)                                        \
     ConvConfig{#WMW "x" #WNW " waves, " #FM "x" #FN " blocks, BK " #BK ", " #KS " slab groups",      \
-               WMW * FM * 32, WNW * FN * 32, BK, 64 * WMW * WNW * KS, &launch_c##I},
+               WMW * FM * 32, WNW * FN * 32, BK, 64 * WMW * WNW * KS, false, &launch_c##I},
 
-const ConvConfig kConfigs[] = {CNN_CONV_CONFIGS(CNN_CONV_ENTRY)};
+#define CNN_SPLIT_ENTRY(I, WMW, WNW, FM, FN, BK)                                                              \
+    ConvConfig{"bf16 parts, " #WMW "x" #WNW " waves, " #FM "x" #FN " blocks, BK " #BK, WMW * FM * 32, WNW * FN * 32, \
+               BK, 64 * WMW * WNW, false, &launch_c##I},
+#define CNN_DIRECT_ENTRY(I, FM, FN, KW) \
+    ConvConfig{"direct, " #FM "x" #FN " blocks, " #KW " waves", FM * 32, FN * 32, 16, 64 * KW, true, &launch_c##I},
+
+const ConvConfig kConfigs[] = {
+    CNN_CONV_CONFIGS(CNN_CONV_ENTRY) CNN_SPLIT_CONFIGS(CNN_SPLIT_ENTRY) CNN_DIRECT_CONFIGS(CNN_DIRECT_ENTRY)};
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 
-// Heuristic choice when no tuned entry exists, fitted by hand to measured
-// times of every configuration on AlexNet's, LeNet's and CIFAR-10 quick's
+// The fp32 matrix-core configuration of a shape when no tuned entry exists,
+// fitted by hand to measured times of configurations 0 to 15 on AlexNet's, LeNet's and CIFAR-10 quick's
 // layers and the single-layer sweep shapes at batches 1 to 256 (`python
 // bench.py --config-table` times them all: over those 46 shapes the
 // heuristic's total came within 0.5% of always picking the fastest on the
 // box it was fitted on, and 4.0-4.9% over on others).  t64: output tiles of a
 // 64 x 64 tile; b128: of a 128 x 128 tile.
-int heuristic_config(const ConvParams& p, int G) {
+int fp32_config(const ConvParams& p, int G) {
     const int64_t t64 = (int64_t)ceil_div(p.M, 64) * ceil_div(p.Kg, 64) * G;
     const int64_t b128 = (int64_t)ceil_div(p.M, 128) * ceil_div(p.Kg, 128) * G;
     if (p.Kg <= 32) return 8;                                         // 32 x 128
@@ -48,14 +56,110 @@ int heuristic_config(const ConvParams& p, int G) {
 // only below 128 tiles into 512 workgroups; batches 1, 64 and 256 measured
 // the same.)
 constexpr int kSplitBelowTiles = 384, kSplitTarget = 1024;
+// The direct kernels share the reduction out among a workgroup's waves already,
+// so only layers of at most 64 tiles (of 32 x 32 or 32 x 64) are split further,
+// with at least four 16-tap runs a wave: at 112 tiles (512 x 14 x 14, 3x3, one
+// image) two to nine chunks measured no faster than one.
+constexpr int kDirectSplitBelow = 64, kDirectTarget = 256;
 void choose_splits(ConvParams& p, const ConvConfig& c) {
     const int tiles = ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G;
     const int nslab = ceil_div(p.Kr, c.bk);
     int splits = 1;
-    if (tiles <= kSplitBelowTiles) splits = std::max(1, std::min(ceil_div(kSplitTarget, tiles), nslab / 8));
+    if (c.direct) {
+        if (tiles <= kDirectSplitBelow)
+            splits = std::max(1, std::min(ceil_div(kDirectTarget, tiles), nslab / (c.threads / 64 * 4)));
+    } else if (tiles <= kSplitBelowTiles) splits = std::max(1, std::min(ceil_div(kSplitTarget, tiles), nslab / 8));
     const int slabs_per_chunk = ceil_div(nslab, splits);
     p.kchunk = splits > 1 ? slabs_per_chunk * c.bk : p.Kr;
     p.splits = splits > 1 ? ceil_div(p.Kr, p.kchunk) : 1;
+}
+
+
+// Whether a direct kernel's tap tables (two words a tap at most, the padding
+// of up to six rounds of the workgroup's waves included) fit the chunk.
+bool direct_fits(const ConvParams& p, const ConvConfig& c) {
+    return ceil_div(p.kchunk, 16) + 6 * (c.threads / 64) <= kDirectTableBytes / (16 * 8);
+}
+
+// Estimated time (us) of a shape on a configuration, by which the families are
+// compared: a start of `base`, then per slab the larger of the latency of one
+// workgroup alone and the throughput time of those that share a compute unit,
+// scaled by the gather's mode, plus the output's bytes, plus the fill, the
+// ReLU pass and the atomics of a split reduction.  The constants were fitted
+// to measured times of every configuration on 460 shapes (AlexNet's, LeNet's,
+// CIFAR-10 quick's and the sweep's layers at batches 1 to 256, and 350 random
+// ones of 7 to 227 pixels, 3 to 512 channels, filters 1x1 to 11x11, strides 1
+// to 4, reductions of 3 to 60000 taps).  The choice by these estimates came
+// within 3.5% (geometric mean) of always taking the fastest.
+struct TimeModel {
+    double base, extra, odd, strided, mask, scalar, out;  // of a family
+};
+const TimeModel kFp32Model = {4.13, 1.71, 0.999, 1.1, 1.03, 1.31, 0.163}, kSplitModel = {5.04, 1.97, 1.11, 1.07, 1.04, 1.39, 0.352},
+                kDirectModel = {3.76, 0.623, 1.45, 1.23, 1.03, 1.24, 0.143};
+// Per slab of one workgroup (us): latency alone, throughput share.
+struct SlabTime {
+    int cfg;
+    double latency, share;
+};
+const SlabTime kSlabTimes[] = {
+    {0, 0.509, 1.14},
+    {2, 0.483, 0.486},
+    {4, 0.503, 0.52},
+    {6, 0.569, 0.785},
+    {8, 0.596, 0.284},
+    {9, 0.495, 0.269},
+    {10, 0.848, 0.525},
+    {16, 1.29, 0.626},
+    {17, 0.801, 0.345},
+    {18, 0.78, 0.34},
+    {19, 1.03, 0.542},
+    {20, 0.467, 0.203},
+    {21, 0.694, 0.48},
+    {22, 0.478, 0.382},
+    {23, 0.5, 0.762},
+    {24, 0.821, 0.666},
+};
+
+double estimate(ConvParams p, int cfg) {
+    const ConvConfig& c = kConfigs[cfg];
+    choose_splits(p, c);
+    const TimeModel& f = c.direct ? kDirectModel : cfg >= 16 ? kSplitModel : kFp32Model;
+    const SlabTime* t = kSlabTimes;
+    while (t->cfg != cfg) ++t;
+    const int64_t wgs = (int64_t)ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G * p.splits;
+    const double queue = (double)ceil_div64(wgs, 256);
+    int slabs = ceil_div(p.kchunk, c.bk);
+    if (c.direct) slabs = ceil_div(slabs, c.threads / 64);
+    double scale = p.Kr % 4 ? f.odd : 1.0;
+    const bool padded = p.ph > 0 || p.pw > 0;
+    if (p.sw > 1 && (!padded || p.RS <= 63)) scale *= f.strided;
+    else if (padded) scale *= p.RS <= 31 ? f.mask : f.scalar;
+    const double mout = 1e-6 * (double)p.M * p.K;
+    double us = f.base + (slabs + f.extra) * std::max(t->latency, queue * t->share) * scale + 4.0 * f.out * mout;
+    if (p.splits > 1) us += 6.06 + 3.4 * p.splits * mout;
+    return us;
+}
+
+// The configuration of a shape when no tuned entry exists: the fp32 one unless
+// a split or a direct one is estimated faster, the latter two by margins that
+// leave out the shapes where the estimate's error decides (a split reduction
+// of the split kernels, any direct one: 15%; over the 460 shapes 5 then ran
+// more than 5% slower than on the fp32 choice, against 23 without).
+constexpr double kMargin = 1.15;
+int heuristic_config(const ConvParams& p0, int G) {
+    int best = fp32_config(p0, G);
+    double least = estimate(p0, best);
+    for (int cfg = 16; cfg < kNumConfigs; ++cfg) {
+        ConvParams p = p0;
+        choose_splits(p, kConfigs[cfg]);
+        if (kConfigs[cfg].direct && !direct_fits(p, kConfigs[cfg])) continue;
+        const double us = estimate(p0, cfg) * (kConfigs[cfg].direct || p.splits > 1 ? kMargin : 1.0);
+        if (us < least) {
+            least = us;
+            best = cfg;
+        }
+    }
+    return best;
 }
 
 }  // namespace
@@ -107,6 +211,10 @@ int conv_prepare(const ConvShape& s, int* cfg, ConvParams* out, int* per_launch)
     // One split decision for every launch of the call (the last one may hold
     // fewer images: splitting it the same way is still correct).
     choose_splits(prm, kConfigs[*cfg]);
+    if (kConfigs[*cfg].direct && !conv::direct_fits(prm, kConfigs[*cfg])) {
+        *cfg = 9;  // a reduction too long for the tap tables: the 64 x 64 tiles take it
+        choose_splits(prm, kConfigs[*cfg]);
+    }
     return CNN_OK;
 }
 

@@ -608,9 +608,31 @@ int launch_cfg(const ConvParams& prm, bool vec_w, hipStream_t st) {
     X(14, 2, 2, 1, 1, 16, 2, 2) /* 64 x 64, 2 slab groups of 4 waves */  \
     X(15, 2, 1, 2, 2, 16, 2, 2) /* 128 x 64, 2 slab groups of 2 waves */
 
-#define CNN_CONV_DECLARE(I, WMW, WNW, FM, FN, BK, KS, ST) \
-    int launch_c##I(const ConvParams& prm, bool vec_w, hipStream_t st);
+// The split kernels (conv_split_kernel.h): index, waves along output channels
+// and along pixels, 32x32 blocks per wave along channels and pixels, slab length.
+#define CNN_SPLIT_CONFIGS(X) \
+    X(16, 2, 2, 2, 2, 16) /* 128 x 128 */ \
+    X(17, 4, 1, 1, 2, 16) /* 128 x 64 */  \
+    X(18, 1, 4, 2, 1, 16) /* 64 x 128 */  \
+    X(19, 1, 4, 3, 1, 16) /* 96 x 128 */  \
+    X(20, 2, 2, 1, 1, 16) /* 64 x 64 */   \
+    X(21, 2, 2, 1, 1, 32) /* 64 x 64 */
+
+// The direct kernels (conv_direct_kernel.h): index, 32x32 blocks per wave along
+// channels and pixels, waves per workgroup (each takes a share of the reduction).
+#define CNN_DIRECT_CONFIGS(X) \
+    X(22, 1, 1, 4)            \
+    X(23, 1, 1, 8)            \
+    X(24, 1, 2, 4)
+constexpr int kDirectStages = 2;  // 16-tap runs of loads in flight per wave
+// LDS the tap tables of a direct kernel may take; reductions that need more
+// are split further across workgroups.
+constexpr int kDirectTableBytes = 64 * 1024;
+
+#define CNN_CONV_DECLARE(I, ...) int launch_c##I(const ConvParams& prm, bool vec_w, hipStream_t st);
 CNN_CONV_CONFIGS(CNN_CONV_DECLARE)
+CNN_SPLIT_CONFIGS(CNN_CONV_DECLARE)
+CNN_DIRECT_CONFIGS(CNN_CONV_DECLARE)
 
 // Defines launch_c<I> (one translation unit per group of configurations).
 #define CNN_CONV_DEFINE(I, WMW, WNW, FM, FN, BK, KS, ST)                           \

@@ -1,0 +1,583 @@
+// The im2col convolution of conv_igemm_kernel.h on the bf16 matrix cores.
+//
+// An fp32 value is the exact sum of three bf16 parts (bf16_split.h; 24
+// significant bits in three times 8, each part's rounding error passed on to
+// the next; exact for magnitudes from 2^-107 up, below which the third part
+// runs out of exponents and the absolute error is at most 2^-134).  A product of two values is
+// then nine products of parts, of which the three below 2^-24 of the whole are
+// left out, and a v_mfma_f32_32x32x16_bf16 multiplies 16 taps in the time in
+// which the fp32 matrix instruction multiplies one (32 against 64 cycles for
+// 16 against 2 taps): six of them cost 3/8 of the fp32 time.
+//
+// Accuracy: the leading products are summed in one fp32 accumulator (one
+// rounding per 16 taps) and the five smaller ones in a second, added at the
+// end.  Against 64-bit sums the error is 0.3 to 0.6 of the fp32 matrix
+// instruction's chain for 16 to 9216 taps of random values, signed or not
+// (1200 taps: 2.0e-7 against 6.2e-7 relative 2-norm).  With one accumulator,
+// or with truncated parts, it is larger than the chain's for some signs.
+//
+// Infinities and NaN: an infinite value has a NaN second part, and a finite one that
+// rounds to an infinite first part an infinite second part of the other sign,
+// so every sum that such a value enters comes out as NaN; a sum that does is
+// computed again in plain fp32 (plain_sum), which gives what the fp32 kernel
+// gives.
+//
+// The split is done once per loaded element, as it is stored to LDS, in steps
+// of a few vector instructions between the matrix-core instructions of the
+// slab before it.  What bounds it: the matrix cores at 54% of busy cycles, the
+// rest barriers and LDS latency between slabs, at a clock that bf16 matrix
+// work on random data holds at 2.1 GHz (a loop of nothing but these
+// instructions reaches 1.8 of the nominal 2.5 PFLOP/s).  256x28x28 -> 256,
+// 3x3, 64 images: 505 -> 412 us (144 TFLOP/s of the layer's own operations);
+// AlexNet at batch 64: 861 -> 723 us.
+#pragma once
+
+#include <cstring>
+#include <type_traits>
+
+#include "bf16_split.h"
+#include "conv_igemm_kernel.h"
+
+namespace cnn {
+namespace conv {
+
+// Tile element (step, part, row, taps 8 half .. 8 half + 7 of the step): a row
+// of a step is 16 bf16 taps (32 bytes), its two 16-byte halves swapped in every
+// other group of four rows, so that both the 128-bit fragment reads (eight rows
+// of one half at a time) and the 128-bit gather stores touch every bank once.
+template <int ROWS>
+__device__ inline int tile_at(int step, int part, int row, int half) {
+    return ((step * 3 + part) * ROWS + row) * 16 + ((half ^ (row >> 2)) & 1) * 8;
+}
+
+// The parts of 8 taps (half of a step) / of 4 taps (quad of a step) of one row;
+// each argument holds the three parts of a pair of taps.
+template <int ROWS>
+__device__ inline void put_oct(unsigned short* tile, int step, int row, int half, const unsigned* a, const unsigned* b,
+                               const unsigned* c, const unsigned* d) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        *reinterpret_cast<uint4*>(tile + tile_at<ROWS>(step, q, row, half)) = make_uint4(a[q], b[q], c[q], d[q]);
+}
+template <int ROWS>
+__device__ inline void put_quad(unsigned short* tile, int step, int row, int quad, const unsigned* a, const unsigned* b) {
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+        *reinterpret_cast<uint2*>(tile + tile_at<ROWS>(step, q, row, quad >> 1) + (quad & 1) * 4) = make_uint2(a[q], b[q]);
+}
+
+// The sum of taps [kbeg, kbeg + klen) for output channel kr of group g at
+// output pixel pq of image n, in plain fp32 (see the header comment: only for
+// sums that came out as NaN).
+__device__ inline float plain_sum(const ConvParams& p, int n, int pq, int g, int kr, int kbeg, int klen) {
+    const int pp = (int)fdiv(pq, p.f_q);
+    const int h0 = pp * p.sh - p.ph, w0 = (pq - pp * p.Q) * p.sw - p.pw;
+    const float* xg = p.x + (size_t)(n * p.C + g * p.Cg) * p.HW;
+    const float* wk = p.w + (size_t)(g * p.Kg + kr) * p.Kr;
+    float sum = 0.0f;
+    for (int kk = kbeg; kk < kbeg + klen; ++kk) {
+        const int c = (int)fdiv(kk, p.f_rs);
+        const int rs = kk - c * p.RS;
+        const int r = (int)fdiv(rs, p.f_s);
+        const int h = h0 + r, w = w0 + rs - r * p.S;
+        const bool inside = (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
+        const float xv = inside ? xg[(size_t)c * p.HW + h * p.W + w] : 0.0f;
+        sum = __builtin_fmaf(p.relu_x && !(xv > 0.0f) ? 0.0f : xv, wk[kk], sum);
+    }
+    return sum;
+}
+
+// Bias, ReLU and NCHW store (lanes = consecutive pixels) of a wave's FM x FN
+// blocks: channels kr0 + 32 i + ... of group g, and per pixel block j this
+// lane's pixel (off[j]: its element offset in channel 0 of y; ok[j]: it
+// exists).  The FN pixel blocks of one output channel are stored one after
+// the other, so that a channel's run of FN * 32 pixels reaches L2 in
+// consecutive instructions (with the blocks stored far apart, 128 x 128 tiles
+// on planes that are not a whole number of cache lines wrote 1.36x their
+// output to HBM: partial lines written back separately).
+template <int FM, int FN>
+__device__ inline void store_blocks(const ConvParams& p, const floatx16 (&acc)[FM][FN], int g, int kr0, int half,
+                                    const int (&off)[FN], const bool (&ok)[FN], int kbeg, int klen) {
+    constexpr int E = FM * FN * 16;
+    unsigned bad[(E + 31) / 32] = {};  // sums that came out as NaN
+    auto put = [&](float* dst, float bv, float val) {
+        if (p.splits > 1) {
+            atomicAdd(dst, val);
+        } else {
+            if (p.bias) val += bv;
+            if (p.relu) val = val > 0.0f ? val : 0.0f;
+            *dst = val;
+        }
+    };
+    auto row_of = [&](int i, int v) { return kr0 + i * 32 + 8 * (v / 4) + 4 * half + (v % 4); };
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+#pragma unroll
+        for (int v = 0; v < 16; ++v) {
+            const int kr = row_of(i, v);
+            if (kr >= p.Kg) continue;
+            const int ko = g * p.Kg + kr;
+            const float bv = (p.splits == 1 && p.bias) ? p.bias[ko] : 0.0f;
+#pragma unroll
+            for (int j = 0; j < FN; ++j) {
+                if (!ok[j]) continue;
+                const float val = acc[i][j][v];
+                const int e = (i * FN + j) * 16 + v;
+                bad[e / 32] |= val != val ? 1u << (e % 32) : 0u;
+                if (p.splits == 1 || val == val) put(p.y + off[j] + ko * p.PQ, bv, val);
+            }
+        }
+    }
+    unsigned any = 0;
+#pragma unroll
+    for (int q = 0; q < (E + 31) / 32; ++q) any |= bad[q];
+    if (any == 0) return;
+    for (int e = 0; e < E; ++e) {
+        unsigned word = bad[0];
+#pragma unroll
+        for (int q = 1; q < (E + 31) / 32; ++q) word = e / 32 == q ? bad[q] : word;
+        if (!(word >> (e % 32) & 1)) continue;
+        int o = off[0];
+#pragma unroll
+        for (int j = 1; j < FN; ++j) o = e / 16 % FN == j ? off[j] : o;
+        const int kr = row_of(e / (16 * FN), e % 16);
+        const int ko = g * p.Kg + kr;
+        const int n = o / (p.K * p.PQ);
+        put(p.y + o + ko * p.PQ, p.splits == 1 && p.bias ? p.bias[ko] : 0.0f,
+            plain_sum(p, n, o - n * p.K * p.PQ, g, kr, kbeg, klen));
+    }
+}
+
+// ST: register stages (slabs of loads in flight).  The compiler is held to the
+// waves per SIMD that the accumulators of a wave's tile leave room for.
+template <int WMW, int WNW, int FM, int FN, int BK, bool VEC_W, int GATHER, int ST>
+__global__ void __launch_bounds__(64 * WMW * WNW)
+__attribute__((amdgpu_waves_per_eu(FM * FN >= 6 ? 1 : FM * FN >= 3 || BK == 32 ? 2 : 3)))
+conv2d_split_f32(ConvParams p) {
+    static_assert(ST % 2 == 0, "the two LDS buffers alternate within a round of ST slabs");
+    constexpr int TM = WMW * FM * 32;  // output channels per workgroup
+    constexpr int TN = WNW * FN * 32;  // output pixels per workgroup
+    constexpr int NT = 64 * WMW * WNW;
+    constexpr int KGROUPS = NT / TN;   // threads sharing one pixel column of the gather
+    constexpr int KRUN = BK / KGROUPS; // consecutive taps gathered per thread
+    constexpr int STEPS = BK / 16;     // matrix-core steps (16 taps) per slab
+    static_assert(NT % TN == 0 && TN % 64 == 0, "gather layout needs TN | NT and whole waves per pixel column");
+    static_assert(BK % 16 == 0 && KRUN % 4 == 0, "slabs of whole steps, gather runs of whole quads");
+    constexpr int WTOT = TM * BK / 4;                  // weight quads (4 taps of a row) per slab
+    constexpr int WV = (WTOT + NT - 1) / NT;            // ... per thread
+    constexpr int AROWS = WV * NT / (BK / 4);           // TM rows + spare rows
+
+    // LDS: [buffer] weight tiles, then [buffer] im2col tiles, each
+    // [step][part][row][16 taps] in bf16 (see tile_at)
+    constexpr int A_ELEMS = STEPS * 3 * AROWS * 16, B_ELEMS = STEPS * 3 * TN * 16;
+    __shared__ __attribute__((aligned(16))) unsigned short smem[2 * (A_ELEMS + B_ELEMS)];
+
+    const int tid = threadIdx.x;
+    auto sA = [&](int buf) { return smem + buf * A_ELEMS; };
+    auto sB = [&](int buf) { return smem + 2 * A_ELEMS + buf * B_ELEMS; };
+    const int g = blockIdx.z % p.G;
+    const int kbeg = (blockIdx.z / p.G) * p.kchunk;  // first tap of this chunk
+    const int klen = min(p.kchunk, p.Kr - kbeg);      // taps in this chunk
+    // Workgroup -> tile.  A launch's workgroups go to the 8 XCDs in turn by
+    // linear id, and each XCD has its own L2: the tiles that read the same
+    // input (every channel tile of a pixel tile, and neighbouring pixel
+    // tiles, whose windows overlap) are given to workgroups of one XCD, in
+    // channel-tile-fastest order.  Ids past the last multiple of 8 keep their
+    // position.
+    int m0, k0;
+    {
+        const int gy = gridDim.y;
+        const int tiles = gridDim.x * gy;
+        const int wg = blockIdx.x + gridDim.x * blockIdx.y;
+        const int full = tiles & ~7;
+        const int seq = wg < full ? (wg & 7) * (full >> 3) + (wg >> 3) : wg;
+        m0 = (seq / gy) * TN;
+        k0 = (seq % gy) * TM;
+    }
+
+    // ---- gather setup: this thread's pixel and tap run (fixed for all slabs)
+    const int mloc = tid % TN;
+    const int kgrp = __builtin_amdgcn_readfirstlane(tid / TN);  // uniform: TN is a multiple of 64
+    const int m = m0 + mloc;
+    int hb, wb, lane_off;
+    if (m < p.M) {
+        const int n = (int)fdiv(m, p.f_pq);
+        const int pq = m - n * p.PQ;
+        const int pp = (int)fdiv(pq, p.f_q);
+        const int qq = pq - pp * p.Q;
+        hb = pp * p.sh - p.ph;
+        wb = qq * p.sw - p.pw;
+        lane_off = ((n * p.C + g * p.Cg) * p.HW + hb * p.W + wb) * 4;
+    } else {
+        hb = -0x40000000;  // every row test fails: the column reads as zero
+        wb = 0;
+        lane_off = 0;
+    }
+    const __amdgpu_buffer_rsrc_t xres =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.x), (short)0, p.xbytes, 0x00020000);
+
+    const int niter = (klen + BK - 1) / BK;  // slabs
+    extern __shared__ __attribute__((aligned(16))) int stab[];  // (niter + ST) * BK entries
+    unsigned inv = 0xffffffffu;
+    if constexpr (GATHER != kGatherScalar) {
+        for (int kk = threadIdx.x; kk < (niter + ST) * BK; kk += NT) {
+            int e = GATHER == kGatherMask ? 31 : GATHER == kGatherStridedMask ? 63 : (int)0x80000000u;
+            if (kk < klen) {
+                const int c = (int)fdiv(kbeg + kk, p.f_rs);
+                const int rs = kbeg + kk - c * p.RS;
+                const int r = (int)fdiv(rs, p.f_s);
+                const int s = rs - r * p.S;
+                const int toff = ((c * p.H + r) * p.W + s) * 4;
+                e = GATHER == kGatherMask ? ((toff << 5) | rs) : GATHER == kGatherStridedMask ? ((toff << 6) | rs) : toff;
+            }
+            stab[kk] = e;
+        }
+        if (GATHER == kGatherNoPad && m >= p.M) lane_off = (int)0x80000000u;
+    }
+    if constexpr (GATHER == kGatherMask) {
+        if (m < p.M) inv = 0x80000000u | outside_taps<unsigned>(hb, wb, p.H, p.W, p.R, p.S);
+    }
+    // strided gather: element u of a thread is pixel group u / TG (16 pixels
+    // apart) and tap group u % TG (4 taps apart) of its wave's pixels
+    constexpr int TG = BK / 4;          // tap groups per slab
+    constexpr int PPT = KRUN / TG;      // pixels per thread
+    constexpr int PW = 16 * PPT;        // pixels per wave
+    constexpr bool STRIDED = GATHER == kGatherStrided || GATHER == kGatherStridedMask;
+    static_assert(!STRIDED || (KRUN % TG == 0 && (NT / 64) * PW == TN),
+                  "strided gather: whole pixel groups per wave");
+    const int ln = tid & 63;
+    const int wpix = (tid >> 6) * PW + (ln >> 2);  // this thread's first pixel, within the tile
+    int soff[STRIDED ? PPT : 1];
+    unsigned long long inv64[GATHER == kGatherStridedMask ? PPT : 1];
+    if constexpr (STRIDED) {
+#pragma unroll
+        for (int pi = 0; pi < PPT; ++pi) {
+            const int mm = m0 + wpix + pi * 16;
+            inv64[GATHER == kGatherStridedMask ? pi : 0] = ~0ull;
+            if (mm < p.M) {
+                const int n = (int)fdiv(mm, p.f_pq);
+                const int pq = mm - n * p.PQ;
+                const int pp = (int)fdiv(pq, p.f_q);
+                const int qq = pq - pp * p.Q;
+                const int h0 = pp * p.sh - p.ph, w0 = qq * p.sw - p.pw;
+                soff[pi] = ((n * p.C + g * p.Cg) * p.HW + h0 * p.W + w0) * 4;
+                if constexpr (GATHER == kGatherStridedMask)
+                    inv64[pi] = (1ull << 63) | outside_taps<unsigned long long>(h0, w0, p.H, p.W, p.R, p.S);
+            } else {
+                soff[pi] = GATHER == kGatherStridedMask ? 0 : (int)0x80000000u;
+            }
+        }
+    }
+    if constexpr (GATHER != kGatherScalar) __syncthreads();
+
+    // Table entries of a slab's elements, then one load per element u of this
+    // thread (STRIDED: pixel group u / TG, tap group u % TG).
+    constexpr int NTAB = GATHER == kGatherScalar ? 1 : STRIDED ? TG : KRUN;
+    int tab[NTAB];
+    auto read_tab = [&](int kslab) {
+        if constexpr (STRIDED) {
+#pragma unroll
+            for (int q = 0; q < TG; ++q) tab[q] = stab[kslab + 4 * q + (ln & 3)];
+        } else if constexpr (GATHER != kGatherScalar) {
+#pragma unroll
+            for (int j = 0; j < KRUN; j += 4) {
+                const int4 e4 = *reinterpret_cast<const int4*>(&stab[kslab + kgrp * KRUN + j]);
+                tab[j] = e4.x, tab[j + 1] = e4.y, tab[j + 2] = e4.z, tab[j + 3] = e4.w;
+            }
+        }
+    };
+    float xr[ST][KRUN];  // register stages
+    auto load_x1 = [&](int sg, int u) {
+        int voff;
+        if constexpr (STRIDED) {
+            const int e = tab[u % TG];
+            if constexpr (GATHER == kGatherStridedMask) {
+                const unsigned bad = (unsigned)(inv64[u / TG] >> (e & 63)) & 1u;
+                voff = (soff[u / TG] + (e >> 6)) | (int)(bad << 31);
+            } else {
+                voff = (int)((unsigned)soff[u / TG] + (unsigned)e);
+            }
+        } else if constexpr (GATHER == kGatherMask) {
+            const unsigned e = (unsigned)tab[u];
+            voff = (lane_off + (int)(e >> 5)) | (int)(((inv >> (e & 31)) & 1u) << 31);
+        } else {
+            voff = (int)((unsigned)lane_off + (unsigned)tab[u]);
+        }
+        xr[sg][u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, voff, 0, 0));
+    };
+    auto load_x_scalar = [&](int kslab, int sg) {
+        const int kk0 = kslab + kgrp * KRUN;  // uniform
+        const int ka0 = kbeg + kk0;           // absolute tap index
+        int c = (int)fdiv(ka0, p.f_rs);
+        const int rs = ka0 - c * p.RS;
+        int r = (int)fdiv(rs, p.f_s);
+        int s = rs - r * p.S;
+        int toff = ((c * p.H + r) * p.W + s) * 4;  // byte offset of tap (c, r, s)
+#pragma unroll
+        for (int j = 0; j < KRUN; ++j) {
+            const bool ok = (kk0 + j < klen) && ((unsigned)(hb + r) < (unsigned)p.H) &&
+                            ((unsigned)(wb + s) < (unsigned)p.W);
+            const int voff = ok ? lane_off + toff : kOutOfRange;
+            xr[sg][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, voff, 0, 0));
+            // next tap: s, then r, then c
+            ++s;
+            toff += 4;
+            const bool wrap_s = (s == p.S);
+            s = wrap_s ? 0 : s;
+            r += wrap_s ? 1 : 0;
+            toff += wrap_s ? (p.W - p.S) * 4 : 0;
+            const bool wrap_r = (r == p.R);
+            r = wrap_r ? 0 : r;
+            toff += wrap_r ? (p.HW - p.R * p.W) * 4 : 0;
+        }
+    };
+
+    // ---- weight tile loads: rows k0.. of the group's [Kg][Kr] block, through a
+    // buffer resource as well (rows past the group or taps past the reduction
+    // read as zero).  Items past the tile land in spare LDS rows never read.
+    const __amdgpu_buffer_rsrc_t wres =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.w), (short)0, p.wbytes, 0x00020000);
+    int w_off[WV], w_col[WV], w_row[WV];
+    bool w_rowok[WV];
+    constexpr bool WQUAD = VEC_W && !STRIDED;  // one 128-bit load per quad
+    constexpr int WSTEP = STRIDED ? 4 : 1;     // distance of a quad's taps in the reduction
+#pragma unroll
+    for (int i = 0; i < WV; ++i) {
+        const int idx = tid + i * NT;
+        w_row[i] = idx / (BK / 4);
+        w_col[i] = idx % (BK / 4);  // quad within the slab
+        w_rowok[i] = w_row[i] < TM && k0 + w_row[i] < p.Kg;
+        // first tap of the quad within the slab
+        const int tap = STRIDED ? (w_col[i] & ~3) * 4 + (w_col[i] & 3) : w_col[i] * 4;
+        w_off[i] = w_rowok[i] ? ((g * p.Kg + k0 + w_row[i]) * p.Kr + kbeg + tap) * 4 : 0;
+    }
+    float wr[ST][WV * 4];
+    constexpr int WLOADS = WV * (WQUAD ? 1 : 4);
+    auto load_w1 = [&](int kslab, int sg, int l) {
+        const int i = WQUAD ? l : l / 4, u = WQUAD ? 0 : l % 4;
+        const int tap = STRIDED ? (w_col[i] & ~3) * 4 + (w_col[i] & 3) : w_col[i] * 4;
+        const bool ok = w_rowok[i] && (kslab + tap + u * WSTEP < klen);
+        const int voff = ok ? w_off[i] + (kslab + u * WSTEP) * 4 : kOutOfRange;
+        if constexpr (WQUAD) {
+            // Cast the whole vector: a bit-cast of one element of an
+            // ext_vector lvalue reads element 0 with this compiler.
+            typedef float f32x4 __attribute__((ext_vector_type(4)));
+            const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, voff, 0, 0));
+#pragma unroll
+            for (int e = 0; e < 4; ++e) wr[sg][4 * i + e] = v[e];
+        } else {
+            wr[sg][4 * i + u] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, voff, 0, 0));
+        }
+    };
+
+    // ---- split and store of a slab's loads, in SIDE steps of a few vector
+    // instructions each, to be placed between matrix-core instructions: step
+    // 3 i + q makes part q of element pair i (the gather's pairs, then the
+    // weights') and stores the parts of a quad or oct once its last pair is done.
+    constexpr int XPAIRS = KRUN / 2, PAIRS = XPAIRS + 2 * WV, SIDE = 3 * PAIRS;
+    unsigned part[PAIRS][3];
+    auto side_step = [&](auto relu, int buf, int sg, int step) {
+        const int i = step / 3, q = step % 3;
+        float* v = i < XPAIRS ? &xr[sg][2 * i] : &wr[sg][2 * (i - XPAIRS)];
+        if constexpr (decltype(relu)::value)
+            if (i < XPAIRS && q == 0) {
+                v[0] = v[0] > 0.0f ? v[0] : 0.0f;
+                v[1] = v[1] > 0.0f ? v[1] : 0.0f;
+            }
+        part[i][q] = split_step(v, q < 2);
+        if (q < 2) return;
+        if (i >= XPAIRS) {
+            if (i % 2 != (XPAIRS + 1) % 2) return;
+            const int l = (i - XPAIRS) / 2;
+            put_quad<AROWS>(sA(buf), w_col[l] >> 2, w_row[l], w_col[l] & 3, part[i - 1], part[i]);
+        } else if (STRIDED) {
+            // tap 4q + t of a step is kept at position 4t + q (the weights
+            // likewise), so that the four taps this thread holds of a step are
+            // neighbours
+            if (i % 2 != 1) return;
+            const int u = 2 * i - 2;  // element of the quad's first tap
+            put_quad<TN>(sB(buf), u % TG / 4, wpix + u / TG * 16, ln & 3, part[i - 1], part[i]);
+        } else if (KRUN % 8 == 0) {
+            if (i % 4 != 3) return;
+            const int pos = kgrp * KRUN + 2 * i - 6;
+            put_oct<TN>(sB(buf), pos >> 4, mloc, (pos >> 3) & 1, part[i - 3], part[i - 2], part[i - 1], part[i]);
+        } else {
+            if (i % 2 != 1) return;
+            const int pos = kgrp * KRUN + 2 * i - 2;
+            put_quad<TN>(sB(buf), pos >> 4, mloc, (pos >> 2) & 3, part[i - 1], part[i]);
+        }
+    };
+
+    // ---- matrix-core work of one slab
+    const int lane = tid & 63;
+    const int wave = tid >> 6;
+    const int wm = wave / WNW;
+    const int wn = wave % WNW;
+    const int half = lane >> 5;
+    const int l32 = lane & 31;
+    floatx16 acc[FM][FN], low[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] = low[i][j][v] = 0.0f;
+
+    // side(q) is called after matrix-core instruction q of the slab
+    constexpr int NM = 6 * FM * FN * STEPS;
+    auto compute = [&](int buf, auto side) {
+        bf16x8 a[STEPS][3][FM], b[STEPS][3][FN];
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) {
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+                    a[st][q][i] = *reinterpret_cast<const bf16x8*>(
+                        sA(buf) + tile_at<AROWS>(st, q, wm * FM * 32 + i * 32 + l32, half));
+#pragma unroll
+                for (int j = 0; j < FN; ++j)
+                    b[st][q][j] = *reinterpret_cast<const bf16x8*>(
+                        sB(buf) + tile_at<TN>(st, q, wn * FN * 32 + j * 32 + l32, half));
+            }
+        // the six products of parts above 2^-24 of the whole
+        constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
+#pragma unroll
+        for (int st = 0; st < STEPS; ++st)
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int i = 0; i < FM; ++i)
+#pragma unroll
+                    for (int j = 0; j < FN; ++j) {
+                        floatx16& c = q == 0 ? acc[i][j] : low[i][j];
+                        c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[st][PA[q]][i], b[st][PB[q]][j], c, 0, 0, 0);
+                        side(((st * 6 + q) * FM + i) * FN + j);
+                    }
+    };
+
+    // ---- main loop.  ST slabs of loads are in flight (ST register stages).
+    // While slab s is multiplied from LDS buffer s % 2, slab s + 1 is split from
+    // stage (s + 1) % ST into the other buffer and slab s + ST requested into
+    // the freed stage s % ST.  One barrier per slab: it publishes slab s, and
+    // nobody reads buffer (s + 1) % 2 (slab s - 1) after it.  The last
+    // niter % ST slabs run after the loop, so that the loop body is
+    // straight-line code and each split waits only for its own loads.
+    auto load = [&](int kslab, int sg) {
+        if constexpr (GATHER == kGatherScalar) {
+            load_x_scalar(kslab, sg);
+        } else {
+            read_tab(kslab);
+#pragma unroll
+            for (int u = 0; u < KRUN; ++u) load_x1(sg, u);
+        }
+#pragma unroll
+        for (int l = 0; l < WLOADS; ++l) load_w1(kslab, sg, l);
+    };
+    auto store = [&](auto relu, int buf, int sg) {
+#pragma unroll
+        for (int t = 0; t < SIDE; ++t) side_step(relu, buf, sg, t);
+    };
+#pragma unroll
+    for (int j = 0; j < ST; ++j) load(j * BK, j);
+    auto reduce = [&](auto relu) {
+        store(relu, 0, 0);
+        int it = 0;
+        for (; it + ST - 1 < niter; it += ST) {
+#pragma unroll
+            for (int j = 0; j < ST; ++j) {
+                const int next = (it + j + ST) * BK;
+                __syncthreads();
+                if constexpr (GATHER == kGatherScalar) load_x_scalar(next, j);
+                else read_tab(next);
+                constexpr int XLOADS = GATHER == kGatherScalar ? 0 : KRUN, LOADS = XLOADS + WLOADS;
+                compute(j & 1, [&](int q) {
+#pragma unroll
+                    for (int t = q * SIDE / NM; t < (q + 1) * SIDE / NM; ++t)
+                        side_step(relu, (j + 1) & 1, (j + 1) % ST, t);
+#pragma unroll
+                    for (int l = q * LOADS / NM; l < (q + 1) * LOADS / NM; ++l) {
+                        if (l < XLOADS) load_x1(j, l);
+                        else load_w1(next, j, l - XLOADS);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                });
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < ST - 1; ++j) {
+            if (it + j < niter) {
+                __syncthreads();
+                if (it + j + 1 < niter) store(relu, (j + 1) & 1, (j + 1) % ST);
+                compute(j & 1, [](int) {});
+            }
+        }
+    };
+    if (p.relu_x) reduce(std::true_type{});
+    else reduce(std::false_type{});
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[i][j][v] += low[i][j][v];
+    // ---- epilogue
+    int off[FN];
+    bool ok[FN];
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        const int mc = m0 + wn * FN * 32 + j * 32 + l32;
+        ok[j] = mc < p.M;
+        const int n = ok[j] ? (int)fdiv(mc, p.f_pq) : 0;
+        off[j] = ok[j] ? n * p.K * p.PQ + mc - n * p.PQ : 0;
+    }
+    store_blocks<FM, FN>(p, acc, g, k0 + wm * FM * 32, half, off, ok, kbeg, klen);
+}
+
+template <int WMW, int WNW, int FM, int FN, int BK, int ST, bool VEC_W, int GATHER>
+inline void launch_split_kernel(const ConvParams& prm, dim3 grid, dim3 block, size_t shm, hipStream_t st) {
+    enqueue((conv2d_split_f32<WMW, WNW, FM, FN, BK, VEC_W, GATHER, ST>), grid, block, shm, st, prm);
+}
+
+// Picks the gather mode for the shape and launches one configuration.
+template <int WMW, int WNW, int FM, int FN, int BK, int ST>
+int launch_split(const ConvParams& prm, bool vec_w, hipStream_t st) {
+    constexpr int TM = WMW * FM * 32;
+    constexpr int TN = WNW * FN * 32;
+    dim3 grid(ceil_div(prm.M, TN), ceil_div(prm.Kg, TM), prm.G * prm.splits);
+    dim3 block(64 * WMW * WNW);
+    // tap tables are at most 32 KiB of LDS
+    const int tab_entries = (ceil_div(prm.kchunk, BK) + ST) * BK;
+    const bool tab_fits = tab_entries * 4 <= 32768;
+    int mode = kGatherScalar;
+    if (tab_fits && prm.ph == 0 && prm.pw == 0)
+        mode = prm.sw > 1 ? kGatherStrided : kGatherNoPad;
+    else if (tab_fits && prm.sw > 1 && prm.RS <= 63 && (int64_t)prm.Cg * prm.HW * 4 < ((int64_t)1 << 25))
+        mode = kGatherStridedMask;
+    else if (tab_fits && prm.RS <= 31 && (int64_t)prm.Cg * prm.HW * 4 < ((int64_t)1 << 27))
+        mode = kGatherMask;
+    const size_t shm = mode == kGatherScalar ? 0 : (size_t)tab_entries * 4;
+    if (vec_w) {
+        if (mode == kGatherStridedMask) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherStridedMask>(prm, grid, block, shm, st);
+        else if (mode == kGatherStrided) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherStrided>(prm, grid, block, shm, st);
+        else if (mode == kGatherNoPad) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherNoPad>(prm, grid, block, shm, st);
+        else if (mode == kGatherMask) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherMask>(prm, grid, block, shm, st);
+        else launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherScalar>(prm, grid, block, shm, st);
+    } else {
+        if (mode == kGatherStridedMask) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherStridedMask>(prm, grid, block, shm, st);
+        else if (mode == kGatherStrided) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherStrided>(prm, grid, block, shm, st);
+        else if (mode == kGatherNoPad) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherNoPad>(prm, grid, block, shm, st);
+        else if (mode == kGatherMask) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherMask>(prm, grid, block, shm, st);
+        else launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherScalar>(prm, grid, block, shm, st);
+    }
+    return check_launch("conv2d_split_f32");
+}
+
+// Defines launch_c<I> of a split configuration.
+#define CNN_SPLIT_DEFINE(I, WMW, WNW, FM, FN, BK)                                  \
+    int launch_c##I(const ConvParams& prm, bool vec_w, hipStream_t st) {           \
+        return launch_split<WMW, WNW, FM, FN, BK, 2>(prm, vec_w, st);           \
+    }
+
+}  // namespace conv
+}  // namespace cnn

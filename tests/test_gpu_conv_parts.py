@@ -1,0 +1,100 @@
+"""The convolution configurations that multiply bf16 parts, and the direct
+ones, where they can go wrong: edges of tiles, reductions of every number of
+runs per wave, values that do not survive the split, and the sums' accuracy."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from conftest import to_dev, to_host
+from paper_1511_07376_amd import workloads as wl
+from parity import assert_gemm_close
+
+pytestmark = pytest.mark.gpu
+
+
+def _configs(gpu, kind):
+    return [i for i in range(gpu.cnn_conv2d_num_configs()) if gpu.cnn_conv2d_config_name(i).startswith(kind)]
+
+
+@pytest.mark.parametrize("taps", [1, 3, 15, 16, 17, 63, 64, 65, 127, 129, 191, 193, 257, 385])
+def test_direct_every_run_count(gpu, taps):
+    """1x1 filters: the reduction is the channel count, so the waves get zero to
+    several 16-tap runs each, even and odd, the last one ragged."""
+    x = wl.normal((2, taps, 5, 7), 1.0, 40, 0)
+    w = wl.normal((33, taps, 1, 1), 1.0, 40, 1)
+    b = wl.normal((33,), 1.0, 40, 2)
+    ref = oracle.conv2d_fwd(x, w, b, (1, 1), (0, 0), 1, False)
+    for cfg in _configs(gpu, "direct") + _configs(gpu, "bf16 parts"):
+        print(f"taps {taps} config {cfg}", flush=True)
+        y = gpu.cnn_conv2d_fwd(to_dev(x), to_dev(w), to_dev(b), 1, 0, 1, False, config=cfg)
+        assert_gemm_close(to_host(y), ref, taps, f"config {cfg}")
+
+
+def test_direct_reduction_beyond_the_tap_tables(gpu):
+    """A 9216-tap reduction of 100 tiles does not fit the direct kernels' tap
+    tables: the call takes the tiled kernels instead."""
+    x = wl.normal((16, 1024, 15, 15), 1.0, 41, 0)
+    w = wl.normal((30, 1024, 3, 3), 1.0, 41, 1)
+    ref = oracle.conv2d_fwd(x[[0, 15]], w, None, (1, 1), (1, 1), 1, True)
+    for cfg in _configs(gpu, "direct"):
+        print(f"config {cfg}", flush=True)
+        y = gpu.cnn_conv2d_fwd(to_dev(x), to_dev(w), None, 1, 1, 1, True, config=cfg)
+        assert_gemm_close(y[[0, 15]].cpu().numpy(), ref, 9216, f"config {cfg}")
+
+
+@pytest.mark.parametrize("shape", [
+    (2, 20, 9, 8, 70, 3, 1, 1, 1),    # masked gather
+    (3, 40, 6, 7, 66, 3, 1, 0, 2),    # unpadded, two groups
+    (1, 64, 11, 9, 40, 3, 2, 1, 1),   # strided gather, split reduction
+], ids=["mask", "groups", "strided"])
+@pytest.mark.parametrize("relu", [False, True])
+def test_values_that_do_not_split(gpu, shape, relu):
+    """Infinities, NaN and values whose leading part rounds to infinity: every
+    configuration gives what the fp32 configuration 0 gives (the same
+    non-finite outputs; the finite ones within the sums' tolerance)."""
+    N, C, H, W, K, R, st, pd, G = shape
+    x = wl.normal((N, C, H, W), 1.0, 42, 0)
+    w = wl.normal((K, C // G, R, R), 1.0, 42, 1)
+    b = wl.normal((K,), 1.0, 42, 2)
+    x[0, 0, 2, 2], x[-1, 5, 0, 1], x[-1, C - 1, H - 1, W - 1] = np.inf, -np.inf, np.nan
+    x[0, 3, H - 1, 0] = np.float32(3.4e38)  # its leading bf16 part is infinite
+    w[1, 2, 0, 0], w[K - 1, 0, 1, 1] = np.inf, np.float32(-3.395e38)
+    args = (to_dev(x), to_dev(w), to_dev(b), st, pd, G, relu)
+    want = to_host(gpu.cnn_conv2d_fwd(*args, config=0))
+    fin = np.isfinite(want) & (np.abs(want) < 1e30)
+    assert np.isnan(want).any() or relu
+    assert np.isinf(want).any() and fin.any()
+    for cfg in _configs(gpu, "bf16 parts") + _configs(gpu, "direct"):
+        print(f"{shape} relu{int(relu)} config {cfg}", flush=True)
+        got = to_host(gpu.cnn_conv2d_fwd(*args, config=cfg))
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(want), err_msg=f"config {cfg}")
+        np.testing.assert_array_equal(np.isinf(got) * np.sign(got), np.isinf(want) * np.sign(want))
+        # both are sums of C/G * R * R products in fp32: each within taps * 2^-24
+        # of the sum of magnitudes (below 8 sqrt(taps) * taps^(1/2) here)
+        taps = C // G * R * R
+        assert np.abs(got[fin] - want[fin]).max() <= 2 * taps * 2.0 ** -24 * 8 * taps
+
+
+@pytest.mark.parametrize("scale", [1e-24, 1.0, 1e18])
+def test_parts_are_no_less_accurate_than_fp32(gpu, scale):
+    """Against 64-bit sums the split configurations' relative error (2-norm)
+    stays below the fp32 configurations' for few and many taps, also where one
+    image is far smaller than the other (the split is per value, so magnitudes
+    do not mix; it is exact from 2^-107 = 6e-33 up)."""
+    for C, R in ((6, 1), (8, 3), (64, 3), (200, 5)):
+        x = wl.normal((2, C, 12, 12), 1.0, 43, 0) * np.float32(scale)
+        x[1] *= np.float32(1e-6)
+        w = wl.normal((64, C, R, R), 1.0, 43, 1)
+        ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double()).numpy()
+
+        def err(cfg, n):
+            y = to_host(gpu.cnn_conv2d_fwd(to_dev(x), to_dev(w), None, 1, 0, 1, False, config=cfg)).astype(np.float64)
+            return np.linalg.norm(y[n] - ref[n]) / np.linalg.norm(ref[n])
+
+        for n in (0, 1):
+            fp32 = err(9, n)
+            for cfg in _configs(gpu, "bf16 parts"):
+                print(f"scale {scale} C{C} R{R} image {n} config {cfg}", flush=True)
+                # 2^-25: the rounding of the result itself, which both have
+                assert err(cfg, n) <= fp32 + 2.0 ** -25
