@@ -228,18 +228,26 @@ __global__ void __launch_bounds__(kThreads) avgpool_f32(PoolParams p) {
 }
 
 // ------------------------------------------------------------------ LRN
-// One thread per (n, chunk of CCH channels, pixel); lanes cover consecutive
-// pixels.  The thread loads its CCH channels plus a halo of HALF channels on
-// each side into registers at once (every load in flight together), then
-// forms each channel's window sum from registers.
-// Splitting the channels into chunks gives the launch enough threads to keep
-// HBM busy even for the 27x27 layers.
+// A wave takes 64 groups of VEC consecutive pixels and a chunk of CCH channels;
+// each work-item loads its CCH channels plus a halo of HALF channels on each
+// side into registers at once (every load in flight together), then forms each
+// channel's window sum from registers.  Bound by HBM: 128-bit loads and stores
+// need 4-byte alignment only, so four pixels a lane are taken on planes of any
+// size from 4 pixels up (the last group of a plane is moved back to end with
+// it; the pixels it shares are written twice, with the same values), and the
+// chunks of the same pixels are neighbouring waves, so that the halo comes from
+// the caches.  64 x 96 x 55 x 55, five channels: 36.4 us with one pixel and 32
+// channels a lane, 33.8 with four and 8 (9 waves a SIMD in flight against 3),
+// 26.2 with non-temporal stores on top (a plain copy of it: 26.9); 12 and 16
+// channels 26.0 and 27.5 there, but 19.2 and 19.6 against 17.0 on 64 x 256 x 27
+// x 27.
 struct LrnParams {
     const float* x;
     float* y;
     int C, HW;
     int nchunk;  // ceil(C / CCH)
-    int total;   // N * nchunk * H*W
+    int total;   // N * pixel groups of a plane
+    FastDiv f_pg;  // division by the pixel groups of a plane
     float alpha_over_size, beta, k;
     int relu_x;  // take the input through a ReLU as it is read
 };
@@ -264,37 +272,75 @@ __device__ inline float lrn_value(const float* w, float k, float alpha_over_size
     return w[WIN / 2] * pow_neg(__builtin_fmaf(alpha_over_size, sq, k), beta);
 }
 
-template <int HALF, int CCH>
+// NT: non-temporal stores.
+template <int HALF, int CCH, int VEC, bool NT>
 __global__ void __launch_bounds__(kThreads) lrn_across_f32(LrnParams p) {
+    typedef float vec __attribute__((ext_vector_type(4)));
+    typedef unsigned uvec __attribute__((ext_vector_type(4)));
     constexpr int WIN = 2 * HALF + 1;
     constexpr int NV = CCH + 2 * HALF;  // channels read per thread
-    // Channels outside [0, C) get an out-of-range buffer offset and read 0:
-    // the NV loads carry no branch, so all of them are in flight at once.
+    constexpr int kAux = NT ? 2 : 0;
+    const int wave = blockIdx.x * (kThreads / 64) + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int item = wave / p.nchunk * 64 + (threadIdx.x & 63);
+    if (item >= p.total) return;
+    const int c0 = wave % p.nchunk * CCH;  // uniform
+    const int n = (int)fdiv(item, p.f_pg);
+    const int pg = item - n * ((p.HW + VEC - 1) / VEC);
+    const int base = (n * p.C * p.HW + min(pg * VEC, p.HW - VEC)) * 4;
+    // The channel's part of the offset is uniform and goes in the load's scalar
+    // offset; for a channel outside [0, C) it is 0x7fffffff, which takes the sum
+    // past the resource, and the load reads 0: no branch, so all NV loads are in
+    // flight at once.
     const __amdgpu_buffer_rsrc_t xres =
         __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.x), (short)0, 0x7fffffff, 0x00020000);
-    for (int64_t t64 = blockIdx.x * kThreads + threadIdx.x; t64 < p.total;
-         t64 += (int64_t)gridDim.x * kThreads) {
-        const int t = (int)t64;
-        const int hw = t % p.HW;
-        const int rest = t / p.HW;
-        const int chunk = rest % p.nchunk;
-        const int n = rest / p.nchunk;
-        const int c0 = chunk * CCH;
-        const int base = n * p.C * p.HW + hw;  // element (n, 0, hw)
-        float v[NV];                            // v[j]: channel c0 - HALF + j
+    const __amdgpu_buffer_rsrc_t yres = __builtin_amdgcn_make_buffer_rsrc(p.y, (short)0, 0x7fffffff, 0x00020000);
+    float v[VEC][NV];  // v[e][j]: pixel e, channel c0 - HALF + j
 #pragma unroll
-        for (int j = 0; j < NV; ++j) {
-            const int cc = c0 - HALF + j;
-            const int off = (unsigned)cc < (unsigned)p.C ? (base + cc * p.HW) * 4 : (int)0x80000000u;
-            v[j] = relu_in(__builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, off, 0, 0)),
-                           p.relu_x);
-        }
-        float* yp = p.y + base;
+    for (int j = 0; j < NV; ++j) {
+        const int cc = c0 - HALF + j;
+        const int soff = (unsigned)cc < (unsigned)p.C ? cc * p.HW * 4 : 0x7fffffff;
+        if constexpr (VEC == 4) {
+            const vec t = __builtin_bit_cast(vec, __builtin_amdgcn_raw_buffer_load_b128(xres, base, soff, 0));
 #pragma unroll
-        for (int i = 0; i < CCH; ++i) {  // window of channel c0 + i: v[i] .. v[i + 2 HALF]
-            if (c0 + i < p.C) yp[(c0 + i) * p.HW] = lrn_value<WIN>(&v[i], p.k, p.alpha_over_size, p.beta);
+            for (int e = 0; e < VEC; ++e) v[e][j] = t[e];
+        } else {
+            v[0][j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, base, soff, 0));
         }
     }
+    if (p.relu_x) {  // uniform
+#pragma unroll
+        for (int e = 0; e < VEC; ++e)
+#pragma unroll
+            for (int j = 0; j < NV; ++j) v[e][j] = relu_in(v[e][j], 1);
+    }
+#pragma unroll
+    for (int i = 0; i < CCH; ++i) {  // window of channel c0 + i: v[.][i] .. v[.][i + 2 HALF]
+        if (c0 + i >= p.C) break;
+        const int soff = (c0 + i) * p.HW * 4;
+        if constexpr (VEC == 4) {
+            vec t;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) t[e] = lrn_value<WIN>(&v[e][i], p.k, p.alpha_over_size, p.beta);
+            __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(uvec, t), yres, base, soff, kAux);
+        } else {
+            const float t = lrn_value<WIN>(&v[0][i], p.k, p.alpha_over_size, p.beta);
+            __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned, t), yres, base, soff, kAux);
+        }
+    }
+}
+
+// nt: an output larger than the eight 4 MiB L2s together, which nothing that
+// follows finds there, is stored past them (16 x 96 x 55 x 55, 18 MB: 8.73 us
+// with plain stores, 8.84 past L2; 74 MB: 33.8 and 26.2).
+template <int HALF>
+void enqueue_lrn(const LrnParams& p, bool vec, bool nt, hipStream_t st) {
+    constexpr int kChunk = 8;
+    LrnParams q = p;
+    q.nchunk = ceil_div(p.C, kChunk);
+    const dim3 grid((unsigned)ceil_div64(ceil_div64(p.total, 64) * q.nchunk, kThreads / 64)), block(kThreads);
+    if (vec && nt) enqueue((lrn_across_f32<HALF, kChunk, 4, true>), grid, block, 0, st, q);
+    else if (vec) enqueue((lrn_across_f32<HALF, kChunk, 4, false>), grid, block, 0, st, q);
+    else enqueue((lrn_across_f32<HALF, kChunk, 1, false>), grid, block, 0, st, q);
 }
 
 // LRN followed by pooling in one pass, for the network executor (an LRN layer
@@ -599,7 +645,6 @@ int launch_lrn(const float* x, int N, int C, int H, int W, int size, float alpha
     p.beta = beta;
     p.k = k;
     if (N == 0) return CNN_OK;
-    constexpr int kChunk = 32;
     const int64_t img = (int64_t)C * p.HW;
     if (size / 2 > 4 || img >= ((int64_t)1 << 29)) {  // wide windows, huge images
         p.nchunk = 1;
@@ -611,19 +656,20 @@ int launch_lrn(const float* x, int N, int C, int H, int W, int size, float alpha
     // The chunked kernel addresses x through a buffer resource with 31-bit
     // byte offsets: fewer than 2^29 elements per launch (whole images).
     const int per_launch = (int)std::min<int64_t>(N, (((int64_t)1 << 29) - 1) / img);
-    p.nchunk = ceil_div(C, kChunk);
+    const bool vec = p.HW >= 4, nt = N * img * 4 > (int64_t)8 * (4 << 20);
+    const int groups = vec ? ceil_div(p.HW, 4) : p.HW;  // of pixels in a plane
+    p.f_pg = make_fastdiv(groups);
     for (int n0 = 0; n0 < N; n0 += per_launch) {
         const int nb = std::min(per_launch, N - n0);
         p.x = x + (size_t)n0 * img;
         p.y = y + (size_t)n0 * img;
-        p.total = nb * p.nchunk * p.HW;
-        const dim3 grid(grid_for(p.total)), block(kThreads);
+        p.total = nb * groups;
         switch (size / 2) {
-            case 0: enqueue((lrn_across_f32<0, kChunk>), grid, block, 0, st, p); break;
-            case 1: enqueue((lrn_across_f32<1, kChunk>), grid, block, 0, st, p); break;
-            case 2: enqueue((lrn_across_f32<2, kChunk>), grid, block, 0, st, p); break;
-            case 3: enqueue((lrn_across_f32<3, kChunk>), grid, block, 0, st, p); break;
-            default: enqueue((lrn_across_f32<4, kChunk>), grid, block, 0, st, p); break;
+            case 0: enqueue_lrn<0>(p, vec, nt, st); break;
+            case 1: enqueue_lrn<1>(p, vec, nt, st); break;
+            case 2: enqueue_lrn<2>(p, vec, nt, st); break;
+            case 3: enqueue_lrn<3>(p, vec, nt, st); break;
+            default: enqueue_lrn<4>(p, vec, nt, st); break;
         }
         const int rc = check_launch("lrn_across_f32");
         if (rc != CNN_OK) return rc;
