@@ -24,6 +24,7 @@
 // (grid z); the partial sums are added with fp32 atomics into an output
 // pre-filled with the bias, and a ReLU, when the layer has one, runs after the
 // last partial sum has landed.
+#include "bf16_split.h"
 #include "common.h"
 #include "fill_jobs.h"
 
@@ -352,6 +353,153 @@ __global__ void __launch_bounds__(64 * KW) fc_direct_f32(FcParams p) {
     }
 }
 
+// The direct kernel on the bf16 matrix cores: every fp32 value is the exact sum
+// of three bf16 parts and six products of parts above 2^-24 of the whole are
+// summed, the leading ones in one accumulator and the rest in another
+// (conv_split_kernel.h has the error analysis).  A wave owns NB blocks of 32
+// images and 32 output features and a run of the reduction; lane (i, h) loads
+// row i of both operands at taps 8q + 4h .. 8q + 4h + 3 of a 32-tap chunk and
+// splits them in its registers, so the loop has neither LDS nor barriers.  The
+// loads need 4-byte alignment only: the one chunk that may end inside (the
+// matrix's last) is loaded tap by tap.
+template <int NB, int KW, bool RELU_X>
+__global__ void __launch_bounds__(64 * KW) fc_parts_f32(FcParams p) {
+    constexpr int Q = 4;  // float4 loads per row and chunk (32 taps)
+    __shared__ float red[KW * NB * 16 * 64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int i = lane & 31, h = lane >> 5;
+    // Workgroup -> (features, images): the image groups of a feature block read
+    // the same weights, so they go to workgroups of one XCD (ids go to the 8
+    // XCDs in turn; those past the last multiple of 8 keep their position).
+    const int ngroups = (p.N + NB * 32 - 1) / (NB * 32);
+    const int wgs = gridDim.x, full = wgs & ~7, wg = blockIdx.x;
+    const int seq = wg < full ? (wg & 7) * (full >> 3) + (wg >> 3) : wg;
+    const int n0 = seq % ngroups * (NB * 32), o0 = seq / ngroups * 32;
+    const int kwg = blockIdx.y * KW * p.kchunk;     // the workgroup's first tap
+    const int kbase = kwg + wave * p.kchunk;        // this wave's first tap
+    const int kend = min(p.I, kbase + p.kchunk);
+    const int nch = kend > kbase ? (kend - kbase) / 32 : 0;  // whole chunks
+    // rows past N (images) or past O (features) lie past the resources' ends
+    const __amdgpu_buffer_rsrc_t xres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(p.x + (size_t)n0 * p.I), (short)0, min(NB * 32, p.N - n0) * p.I * 4, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wres = __builtin_amdgcn_make_buffer_rsrc(
+        const_cast<float*>(p.w + (size_t)o0 * p.I), (short)0, min(32, p.O - o0) * p.I * 4, 0x00020000);
+    const int row = (i * p.I + 4 * h) * 4;  // byte offset of this lane's row and half
+    const int block = 32 * p.I * 4;         // ... of the next 32 rows
+
+    floatx16 acc[NB], low[NB];
+#pragma unroll
+    for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[nb][v] = low[nb][v] = 0.0f;
+    f32x4 xa[2][NB][Q], wb[2][Q];
+    auto load = [&](int c, int s) {
+        const int soff = (kbase + c * 32) * 4;
+#pragma unroll
+        for (int q = 0; q < Q; ++q) {
+            wb[s][q] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(wres, row + 32 * q, soff, 0));
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb)
+                xa[s][nb][q] = __builtin_bit_cast(
+                    f32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, row + nb * block + 32 * q, soff, 0));
+        }
+    };
+    auto parts = [](f32x4 u, f32x4 v, bool relu, bf16x8* out) {
+        float t[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
+        typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+        u32x4 w[3];
+#pragma unroll
+        for (int e = 0; e < 8; ++e)
+            if (relu) t[e] = t[e] > 0.0f ? t[e] : 0.0f;
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int q = 0; q < 3; ++q) w[q][e] = split_step(t + 2 * e, q < 2);
+#pragma unroll
+        for (int q = 0; q < 3; ++q) out[q] = __builtin_bit_cast(bf16x8, w[q]);
+    };
+    auto compute = [&](int s) {
+        constexpr int PA[6] = {0, 0, 1, 1, 0, 2}, PB[6] = {0, 1, 0, 1, 2, 0};
+#pragma unroll
+        for (int st = 0; st < Q / 2; ++st) {
+            bf16x8 a[NB][3], b[3];
+            parts(wb[s][2 * st], wb[s][2 * st + 1], false, b);
+#pragma unroll
+            for (int nb = 0; nb < NB; ++nb) parts(xa[s][nb][2 * st], xa[s][nb][2 * st + 1], RELU_X, a[nb]);
+#pragma unroll
+            for (int q = 0; q < 6; ++q)
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb) {
+                    floatx16& c = q == 0 ? acc[nb] : low[nb];
+                    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[nb][PA[q]], b[PB[q]], c, 0, 0, 0);
+                }
+        }
+    };
+    if (nch > 0) {
+        load(0, 0);
+        int c = 0;
+        for (; c + 1 < nch; c += 2) {
+            load(c + 1, 1);
+            compute(0);
+            load(min(c + 2, nch - 1), 0);  // past the run: the last chunk once more, not multiplied
+            compute(1);
+        }
+        if (c < nch) compute(0);
+    }
+    const int kt = kbase + nch * 32;  // a chunk that ends inside
+    if (kt < kend) {
+#pragma unroll
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const int at = kt + 8 * q + 4 * h + e < kend ? row + 32 * q + 4 * (kt + e) : kOutOfRange;
+                wb[0][q][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, at, 0, 0));
+#pragma unroll
+                for (int nb = 0; nb < NB; ++nb)
+                    xa[0][nb][q][e] = __builtin_bit_cast(
+                        float, __builtin_amdgcn_raw_buffer_load_b32(xres, at < 0 ? at : at + nb * block, 0, 0));
+            }
+        compute(0);
+    }
+
+    // the waves' partial tiles, summed in wave order (lanes on consecutive words)
+#pragma unroll
+    for (int t = 0; t < NB; ++t)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) red[(wave * NB * 16 + t * 16 + v) * 64 + lane] = acc[t][v] + low[t][v];
+    __syncthreads();
+    constexpr int E = NB * 16 * 64;
+    const bool split = gridDim.y > 1;
+    for (int e = threadIdx.x; e < E; e += 64 * KW) {
+        float sum = red[e];
+#pragma unroll
+        for (int w = 1; w < KW; ++w) sum += red[w * E + e];
+        const int t = e >> 10, v = (e >> 6) & 15, l = e & 63;
+        const int n = n0 + t * 32 + 8 * (v >> 2) + 4 * (l >> 5) + (v & 3);
+        const int o = o0 + (l & 31);
+        if (n >= p.N || o >= p.O) continue;
+        if (!(__builtin_fabsf(sum) <= 3.402823466e38f)) {
+            // a value that does not split (infinite, NaN, or rounding to an
+            // infinite part) or an overflow: the sum in plain fp32
+            const int ke = (int)min((int64_t)p.I, (int64_t)kwg + (int64_t)KW * p.kchunk);
+            sum = 0.0f;
+            for (int k = kwg; k < ke; ++k) {
+                float xv = p.x[(size_t)n * p.I + k];
+                if constexpr (RELU_X) xv = xv > 0.0f ? xv : 0.0f;
+                sum = __builtin_fmaf(xv, p.w[(size_t)o * p.I + k], sum);
+            }
+        }
+        float* dst = p.y + (size_t)n * p.O + o;
+        if (split) {
+            atomicAdd(dst, sum);
+        } else {
+            if (p.bias) sum += p.bias[o];
+            if (p.relu) sum = sum > 0.0f ? sum : 0.0f;
+            *dst = sum;
+        }
+    }
+}
+
 // Batches of at most kGemvMaxN images: a matrix-vector product per image on
 // the vector ALUs, since a 32-row MFMA tile would be mostly empty.  A
 // workgroup owns R consecutive output features (4, or 1 when there are fewer
@@ -561,6 +709,45 @@ int launch_fc_direct(const FcParams& prm, bool relu_in, hipStream_t st, bool* re
                    : launch_fc_direct_t<2, OB, KW, false>(prm, st, relu_left, prefilled);
 }
 
+// Direct kernels on bf16 parts: workgroups of kPartsWaves waves along the
+// reduction for 32 features and up to 64 images; split (over workgroups) until
+// `target` of them run, each wave keeping at least two chunks.
+constexpr int kPartsWaves = 8, kPartsTarget = 256;
+int fc_parts_split(int target, int N, int I, int O, int* kchunk) {
+    const int groups = ceil_div(O, 32) * ceil_div(N, N <= 32 ? 32 : 64);
+    const int splits = std::max(1, std::min(target / groups, I / (kPartsWaves * 64)));
+    *kchunk = ceil_div(ceil_div(I, splits * kPartsWaves), 32) * 32;  // whole chunks
+    return ceil_div(I, kPartsWaves * *kchunk);
+}
+
+int launch_fc_parts(const FcParams& prm0, int target, bool relu_in, hipStream_t st, bool* relu_left, bool prefilled) {
+    FcParams prm = prm0;
+    const int splits = fc_parts_split(target, prm.N, prm.I, prm.O, &prm.kchunk);
+    const int nb = prm.N <= 32 ? 1 : 2;
+    const int64_t wgs = (int64_t)ceil_div(prm.O, 32) * ceil_div(prm.N, nb * 32);
+    if (wgs * 64 * kPartsWaves >= ((int64_t)1 << 32))
+        return fail(CNN_ERR_UNSUPPORTED, "fc: %d x %d outputs exceed this configuration's grid", prm.N, prm.O);
+    const dim3 grid((unsigned)wgs, splits), block(64 * kPartsWaves);
+    if (splits > 1 && !prefilled) {
+        const int rc = fill_fc_bias(prm, st);
+        if (rc != CNN_OK) return rc;
+    }
+    if (nb == 1) {
+        if (relu_in) enqueue((fc_parts_f32<1, kPartsWaves, true>), grid, block, 0, st, prm);
+        else enqueue((fc_parts_f32<1, kPartsWaves, false>), grid, block, 0, st, prm);
+    } else {
+        if (relu_in) enqueue((fc_parts_f32<2, kPartsWaves, true>), grid, block, 0, st, prm);
+        else enqueue((fc_parts_f32<2, kPartsWaves, false>), grid, block, 0, st, prm);
+    }
+    const int rc = check_launch("fc_parts_f32");
+    if (rc != CNN_OK || splits == 1 || !prm.relu) return rc;
+    if (relu_left) {  // the caller applies it
+        *relu_left = true;
+        return CNN_OK;
+    }
+    return launch_relu(prm.y, prm.y, (int64_t)prm.N * prm.O, st);
+}
+
 // The configurations (cnn_fc_fwd_config).
 struct FcConfig {
     const char* name;
@@ -573,6 +760,8 @@ const FcConfig kFcConfigs[] = {
     {"direct, 32 features per wave, 8 waves", 64, true},
     {"matrix-vector", kGemvMaxN, false},
     {"tiled, 64 images x 64 features, 2x2 waves, 32-tap slabs", 1 << 30, false},
+    {"bf16 parts, 32 features, 8 waves", 1 << 30, false},
+    {"bf16 parts, 32 features, 8 waves, split reduction", 1 << 30, false},
 };
 constexpr int kNumFcConfigs = sizeof(kFcConfigs) / sizeof(kFcConfigs[0]);
 
@@ -595,12 +784,29 @@ constexpr int kNumFcConfigs = sizeof(kFcConfigs) / sizeof(kFcConfigs[0]);
 // same split count, twice the matrix-core work per barrier): AlexNet's fc6
 // at batch 64 went from 45 to 43 us in the network; fc8 keeps 16-tap slabs,
 // whose finer split granule gives it twice the splits.
+//
+// Short reductions (up to 768 features in, 1000 for at most 32 images) that the
+// fp32 direct kernel does not take run on bf16 parts, unsplit: one launch,
+// where the tiled kernels split the reduction and then fill, add and rectify
+// in three.  Over 22 shapes of 3 to 256 images, 64 to 1000 features in and 10
+// to 4096 out: 3.7 to 11.1 us against 5.1 to 18 (610 -> 188 at 230 images 14.1
+// -> 8.1, 512 -> 4096 at 64 13.3 -> 11.1; 512 -> 512 at 200 10.7 -> 10.9).  The
+// fp32 direct kernel's shapes stay with it: by themselves 800 -> 500 at 16
+// images took 9.0 against 7.6 us, but in LeNet, where the fill and the ReLU
+// cost it nothing, the network ran 3 us faster with it.  Longer reductions are
+// bound by the 32-row loads (1024 -> 64 at 64 images 10.0 -> 16.0, 9216 -> 4096
+// 54 -> 80 split), except for at most 32 images with rows that are not whole
+// 16-byte vectors, which leave the tiled kernels 32-bit loads: split, 2600 to
+// 9200 features in and up to 2048 out, 8.6 to 15.4 us against 12.8 to 18.2.
 int fc_heuristic(int N, int I, int O, bool vec) {
     if (N <= kGemvMaxN) return 3;
-    if (N > 32 && N <= 64 && O >= 2048 && I >= 4096) return 4;
     if (vec && N <= 64 && I <= 4096 && O <= (N <= 32 ? 2048 : 512)) return 2;
+    const bool grid = (int64_t)ceil_div(O, 32) * ceil_div(N, 32) < (1 << 20);  // within a launch's limits
+    if (grid && I <= (N <= 32 ? 1000 : 768)) return 5;
+    if (grid && N <= 32 && !vec && O <= 2048) return 6;
+    if (N > 32 && N <= 64 && O >= 2048 && I >= 4096) return 4;
     if (N <= 32) return 1;
-    if (N > 64 && O <= 1024 && I >= 256) return 1;
+    if (N > 64 && O <= 1024) return 1;
     return 0;
 }
 
@@ -611,6 +817,8 @@ int fc_config_splits(int cfg, int N, int I, int O) {
         case 1: return fc_split(fc_geom(32, N), N, I, O, &kchunk);
         case 2: return fc_direct_split(FcDirectGeom{1, 8}, I, O, &kchunk);
         case 4: return fc_split(fc_geom(64, N, 32), N, I, O, &kchunk);
+        case 5: return fc_parts_split(1, N, I, O, &kchunk);
+        case 6: return fc_parts_split(kPartsTarget, N, I, O, &kchunk);
         default: return 1;
     }
 }
@@ -682,6 +890,8 @@ int launch_fc(const float* x, int N, int I, const float* w, const float* bias, i
         case 1: return CNN_FC_CFG(fc_geom(32, N), 1, 4, 1, 1, 32, 4);  // 32 images x 128 features
         case 2: return launch_fc_direct<1, 8>(prm, relu_in, st, relu_left, prefilled);
         case 4: return CNN_FC_CFG(fc_geom(64, N, 32), 2, 2, 1, 1, 32, 4);  // 64 x 64, 32-tap slabs
+        case 5: return launch_fc_parts(prm, 1, relu_in, st, relu_left, prefilled);
+        case 6: return launch_fc_parts(prm, kPartsTarget, relu_in, st, relu_left, prefilled);
         default:
             static_assert(kGemvMaxN == 2, "one instantiation per batch size");
             return N == 1 ? launch_fc_gemv<1>(prm, vec, relu_in, st) : launch_fc_gemv<2>(prm, vec, relu_in, st);

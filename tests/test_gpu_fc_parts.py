@@ -1,0 +1,63 @@
+"""Fully connected layers on bf16 parts where they can go wrong: ragged blocks
+of images and features, waves with no, one or a partial 32-tap chunk, rows of
+any alignment, values that do not survive the split, and accuracy."""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from conftest import to_dev, to_host
+from paper_1511_07376_amd import workloads as wl
+from parity import assert_gemm_close
+
+pytestmark = pytest.mark.gpu
+
+
+def _configs(gpu):
+    return [i for i in range(gpu.cnn_fc_num_configs()) if gpu.cnn_fc_config_name(i).startswith("bf16 parts")]
+
+
+@pytest.mark.parametrize("N", [3, 32, 33, 65, 129])
+@pytest.mark.parametrize("I", [1, 31, 32, 33, 255, 257, 515, 1000, 1023, 1025, 2049])
+def test_fc_parts_edges(gpu, N, I):
+    O = 31 if N == 65 else 70
+    x, w, b = wl.normal((N, I), 1.0, 60, 0), wl.normal((O, I), 1.0, 60, 1), wl.normal((O,), 1.0, 60, 2)
+    for relu in (False, True):
+        ref = oracle.fc_fwd(x, w, b, relu)
+        for cfg in [-1] + _configs(gpu):
+            print(f"N{N} I{I} relu{int(relu)} config {cfg}", flush=True)
+            y = gpu.cnn_fc_fwd(to_dev(x), to_dev(w), to_dev(b), relu, config=cfg)
+            assert_gemm_close(to_host(y), ref, I, f"N{N} I{I} relu{int(relu)} config {cfg}")
+
+
+@pytest.mark.parametrize("I", [40, 1100])
+def test_fc_parts_values_that_do_not_split(gpu, I):
+    """Infinities, NaN and a value whose leading part rounds to infinity: the
+    same non-finite outputs as the fp32 tiles give."""
+    x, w = wl.normal((5, I), 1.0, 61, 0), wl.normal((37, I), 1.0, 61, 1)
+    x[0, 2], x[1, I - 1], x[2, 7], x[3, 11] = np.inf, -np.inf, np.nan, np.float32(3.4e38)
+    w[4, 3], w[36, 0] = -np.inf, np.float32(-3.395e38)
+    args = to_dev(x), to_dev(w), None, False
+    want = to_host(gpu.cnn_fc_fwd(*args, config=0))
+    fin = np.isfinite(want) & (np.abs(want) < 1e30)
+    assert np.isnan(want).any() and np.isinf(want).any() and fin.any()
+    for cfg in _configs(gpu):
+        got = to_host(gpu.cnn_fc_fwd(*args, config=cfg))
+        np.testing.assert_array_equal(np.isnan(got), np.isnan(want))
+        np.testing.assert_array_equal(np.isinf(got) * np.sign(got), np.isinf(want) * np.sign(want))
+        # each a sum of I products in fp32, within I * 2^-24 of the sum of magnitudes (below 8 I here)
+        assert np.abs(got[fin] - want[fin]).max() <= 2 * I * 2.0 ** -24 * 8 * I
+
+
+@pytest.mark.parametrize("I", [6, 333, 4000])
+def test_fc_parts_no_less_accurate_than_fp32(gpu, I):
+    x, w = wl.normal((24, I), 1.0, 62, 0), wl.normal((96, I), 1.0, 62, 1)
+    ref = (torch.from_numpy(x).double() @ torch.from_numpy(w).double().t()).numpy()
+
+    def err(cfg):
+        y = to_host(gpu.cnn_fc_fwd(to_dev(x), to_dev(w), None, False, config=cfg)).astype(np.float64)
+        return np.linalg.norm(y - ref) / np.linalg.norm(ref)
+
+    for cfg in _configs(gpu):
+        # 2^-25: the rounding of the result itself, which both have
+        assert err(cfg) <= err(0) + 2.0 ** -25
