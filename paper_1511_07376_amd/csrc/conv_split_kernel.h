@@ -16,11 +16,12 @@
 // (1200 taps: 2.0e-7 against 6.2e-7 relative 2-norm).  With one accumulator,
 // or with truncated parts, it is larger than the chain's for some signs.
 //
-// Infinities and NaN: an infinite value has a NaN second part, and a finite one that
-// rounds to an infinite first part an infinite second part of the other sign,
-// so every sum that such a value enters comes out as NaN; a sum that does is
-// computed again in plain fp32 (plain_sum), which gives what the fp32 kernel
-// gives.
+// Infinities, NaN and the end of the range: an infinite value has a NaN second
+// part, a finite one that rounds to an infinite first part an infinite second
+// part of the other sign, and the leading products of finite values can
+// overflow where their sum does not (their parts round up).  Every such sum
+// comes out as infinity or NaN; a sum that does is computed again in plain fp32
+// (repair_sums), which gives what the fp32 kernel gives.
 //
 // The split is done once per loaded element, as it is stored to LDS, in steps
 // of a few vector instructions between the matrix-core instructions of the
@@ -66,25 +67,52 @@ __device__ inline void put_quad(unsigned short* tile, int step, int row, int qua
         *reinterpret_cast<uint2*>(tile + tile_at<ROWS>(step, q, row, quad >> 1) + (quad & 1) * 4) = make_uint2(a[q], b[q]);
 }
 
-// The sum of taps [kbeg, kbeg + klen) for output channel kr of group g at
-// output pixel pq of image n, in plain fp32 (see the header comment: only for
-// sums that came out as NaN).
-__device__ inline float plain_sum(const ConvParams& p, int n, int pq, int g, int kr, int kbeg, int klen) {
-    const int pp = (int)fdiv(pq, p.f_q);
-    const int h0 = pp * p.sh - p.ph, w0 = (pq - pp * p.Q) * p.sw - p.pw;
-    const float* xg = p.x + (size_t)(n * p.C + g * p.Cg) * p.HW;
-    const float* wk = p.w + (size_t)(g * p.Kg + kr) * p.Kr;
-    float sum = 0.0f;
-    for (int kk = kbeg; kk < kbeg + klen; ++kk) {
-        const int c = (int)fdiv(kk, p.f_rs);
-        const int rs = kk - c * p.RS;
-        const int r = (int)fdiv(rs, p.f_s);
-        const int h = h0 + r, w = w0 + rs - r * p.S;
-        const bool inside = (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
-        const float xv = inside ? xg[(size_t)c * p.HW + h * p.W + w] : 0.0f;
-        sum = __builtin_fmaf(p.relu_x && !(xv > 0.0f) ? 0.0f : xv, wk[kk], sum);
+// Replaces the sums of a wave's FM x FN blocks that are not finite by the plain
+// fp32 sums of the same taps (see the header comment).  Arguments as of
+// store_blocks.  A column of sums shares its pixel's window, read once per tap.
+template <int FM, int FN>
+__device__ inline void repair_sums(const ConvParams& p, floatx16 (&acc)[FM][FN], int g, int kr0, int half,
+                                   const int (&off)[FN], const bool (&ok)[FN], int kbeg, int klen) {
+#pragma unroll
+    for (int j = 0; j < FN; ++j) {
+        float nan = 0.0f;  // NaN if any sum of the column is not finite
+#pragma unroll
+        for (int i = 0; i < FM; ++i)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) nan = __builtin_fmaf(acc[i][j][v], 0.0f, nan);
+        if (!ok[j] || nan == 0.0f) continue;
+        const int n = off[j] / (p.K * p.PQ), pq = off[j] - n * p.K * p.PQ;
+        const int pp = (int)fdiv(pq, p.f_q);
+        const int h0 = pp * p.sh - p.ph, w0 = (pq - pp * p.Q) * p.sw - p.pw;
+        const float* xg = p.x + (size_t)(n * p.C + g * p.Cg) * p.HW;
+        const float* wg = p.w + (size_t)g * p.Kg * p.Kr;
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const int kr = kr0 + i * 32 + 4 * half;  // of sum v: kr + 8 (v / 4) + v % 4
+            float sum[16];
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[v] = 0.0f;
+            for (int kk = kbeg; kk < kbeg + klen; ++kk) {
+                const int c = (int)fdiv(kk, p.f_rs);
+                const int rs = kk - c * p.RS;
+                const int r = (int)fdiv(rs, p.f_s);
+                const int h = h0 + r, w = w0 + rs - r * p.S;
+                const bool inside = (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
+                float xv = inside ? xg[(size_t)c * p.HW + h * p.W + w] : 0.0f;
+                if (p.relu_x) xv = xv > 0.0f ? xv : 0.0f;
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {  // rows past the group: its last one, not stored
+                    const int row = min(kr + 8 * (v / 4) + v % 4, p.Kg - 1);
+                    sum[v] = __builtin_fmaf(xv, wg[(size_t)row * p.Kr + kk], sum[v]);
+                }
+            }
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const bool finite = __builtin_fabsf(acc[i][j][v]) <= 3.402823466e38f;
+                acc[i][j][v] = finite ? acc[i][j][v] : sum[v];
+            }
+        }
     }
-    return sum;
 }
 
 // Bias, ReLU and NCHW store (lanes = consecutive pixels) of a wave's FM x FN
@@ -97,54 +125,29 @@ __device__ inline float plain_sum(const ConvParams& p, int n, int pq, int g, int
 // output to HBM: partial lines written back separately).
 template <int FM, int FN>
 __device__ inline void store_blocks(const ConvParams& p, const floatx16 (&acc)[FM][FN], int g, int kr0, int half,
-                                    const int (&off)[FN], const bool (&ok)[FN], int kbeg, int klen) {
-    constexpr int E = FM * FN * 16;
-    unsigned bad[(E + 31) / 32] = {};  // sums that came out as NaN
-    auto put = [&](float* dst, float bv, float val) {
-        if (p.splits > 1) {
-            atomicAdd(dst, val);
-        } else {
-            if (p.bias) val += bv;
-            if (p.relu) val = val > 0.0f ? val : 0.0f;
-            *dst = val;
-        }
-    };
-    auto row_of = [&](int i, int v) { return kr0 + i * 32 + 8 * (v / 4) + 4 * half + (v % 4); };
+                                    const int (&off)[FN], const bool (&ok)[FN]) {
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
-            const int kr = row_of(i, v);
+            const int kr = kr0 + i * 32 + 8 * (v / 4) + 4 * half + (v % 4);
             if (kr >= p.Kg) continue;
             const int ko = g * p.Kg + kr;
             const float bv = (p.splits == 1 && p.bias) ? p.bias[ko] : 0.0f;
 #pragma unroll
             for (int j = 0; j < FN; ++j) {
                 if (!ok[j]) continue;
-                const float val = acc[i][j][v];
-                const int e = (i * FN + j) * 16 + v;
-                bad[e / 32] |= val != val ? 1u << (e % 32) : 0u;
-                if (p.splits == 1 || val == val) put(p.y + off[j] + ko * p.PQ, bv, val);
+                float* dst = p.y + off[j] + ko * p.PQ;
+                float val = acc[i][j][v];
+                if (p.splits > 1) {
+                    atomicAdd(dst, val);
+                } else {
+                    if (p.bias) val += bv;
+                    if (p.relu) val = val > 0.0f ? val : 0.0f;
+                    *dst = val;
+                }
             }
         }
-    }
-    unsigned any = 0;
-#pragma unroll
-    for (int q = 0; q < (E + 31) / 32; ++q) any |= bad[q];
-    if (any == 0) return;
-    for (int e = 0; e < E; ++e) {
-        unsigned word = bad[0];
-#pragma unroll
-        for (int q = 1; q < (E + 31) / 32; ++q) word = e / 32 == q ? bad[q] : word;
-        if (!(word >> (e % 32) & 1)) continue;
-        int o = off[0];
-#pragma unroll
-        for (int j = 1; j < FN; ++j) o = e / 16 % FN == j ? off[j] : o;
-        const int kr = row_of(e / (16 * FN), e % 16);
-        const int ko = g * p.Kg + kr;
-        const int n = o / (p.K * p.PQ);
-        put(p.y + o + ko * p.PQ, p.splits == 1 && p.bias ? p.bias[ko] : 0.0f,
-            plain_sum(p, n, o - n * p.K * p.PQ, g, kr, kbeg, klen));
     }
 }
 
@@ -531,7 +534,9 @@ conv2d_split_f32(ConvParams p) {
         const int n = ok[j] ? (int)fdiv(mc, p.f_pq) : 0;
         off[j] = ok[j] ? n * p.K * p.PQ + mc - n * p.PQ : 0;
     }
-    store_blocks<FM, FN>(p, acc, g, k0 + wm * FM * 32, half, off, ok, kbeg, klen);
+    const int kr0 = k0 + wm * FM * 32;
+    repair_sums<FM, FN>(p, acc, g, kr0, half, off, ok, kbeg, klen);
+    store_blocks<FM, FN>(p, acc, g, kr0, half, off, ok);
 }
 
 template <int WMW, int WNW, int FM, int FN, int BK, int ST, bool VEC_W, int GATHER>

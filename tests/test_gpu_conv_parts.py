@@ -98,3 +98,26 @@ def test_parts_are_no_less_accurate_than_fp32(gpu, scale):
                 print(f"scale {scale} C{C} R{R} image {n} config {cfg}", flush=True)
                 # 2^-25: the rounding of the result itself, which both have
                 assert err(cfg, n) <= fp32 + 2.0 ** -25
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+@pytest.mark.parametrize("taps", [1, 2, 24, 512], ids=lambda t: f"taps{t}")
+def test_sums_just_inside_the_range(gpu, taps, sign):
+    """Sums within 0.1% of the largest float, of inputs whose leading parts
+    round up: the leading products (1 tap) or their sum (2, 24 and 512 taps,
+    the last one split over workgroups) overflow where the sum itself does not.
+    Every configuration gives the finite value."""
+    x = np.zeros((2, taps, 4, 5), np.float32)
+    live = min(1 << (taps.bit_length() - 1), 16)  # the rest of the taps is zero: the sum stays in one chunk
+    x[0, :live] = np.float32(1.998 * 2.0 ** 63 / live)
+    x[1] = 1.0
+    w = np.full((40, taps, 1, 1), sign * 2.0 ** 64, np.float32)
+    w[1::2] = 1.0
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double()).numpy()
+    assert 3.39e38 < np.abs(ref).max() < 3.4e38
+    for cfg in [0, 9] + _configs(gpu, "bf16 parts") + _configs(gpu, "direct"):
+        print(f"taps {taps} sign {sign} config {cfg}", flush=True)
+        got = to_host(gpu.cnn_conv2d_fwd(to_dev(x), to_dev(w), None, 1, 0, 1, False, config=cfg))
+        assert np.isfinite(got).all(), f"config {cfg}"
+        # products of one sign: each sum within (taps - 1) roundings and the products' own
+        assert (np.abs(got - ref) <= taps * 2.0 ** -23 * np.abs(ref)).all(), f"config {cfg}"
