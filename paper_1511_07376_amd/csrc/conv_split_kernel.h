@@ -503,7 +503,11 @@ conv2d_split_f32(ConvParams p) {
                         if (l < XLOADS) load_x1(j, l);
                         else load_w1(next, j, l - XLOADS);
                     }
-                    __builtin_amdgcn_sched_barrier(0);
+                    // The strided gathers keep the compiler's order, as in
+                    // conv_igemm_kernel.h: there a pinned order returned a tap
+                    // as zero when workgroups shared a compute unit, for a
+                    // reason that was not established.
+                    if constexpr (!STRIDED) __builtin_amdgcn_sched_barrier(0);
                 });
             }
         }

@@ -121,3 +121,23 @@ def test_sums_just_inside_the_range(gpu, taps, sign):
         assert np.isfinite(got).all(), f"config {cfg}"
         # products of one sign: each sum within (taps - 1) roundings and the products' own
         assert (np.abs(got - ref) <= taps * 2.0 ** -23 * np.abs(ref)).all(), f"config {cfg}"
+
+
+@pytest.mark.parametrize("batch", [16, 64])
+@pytest.mark.parametrize("shape", [(3, 227, 96, 11, 4, 0), (3, 224, 64, 7, 2, 3)], ids=["11x11s4", "7x7s2p3"])
+def test_strided_stems_every_output(gpu, shape, batch):
+    """The strided gathers of large launches, whose workgroups share compute
+    units: every output of every configuration against configuration 9."""
+    C, H, K, R, st, pd = shape
+    gen = torch.Generator(device="cuda").manual_seed(44)
+    x = torch.randn((batch, C, H, H), generator=gen, device="cuda")
+    w = torch.randn((K, C, R, R), generator=gen, device="cuda")
+    want = gpu.cnn_conv2d_fwd(x, w, None, st, pd, 1, False, config=9)
+    # two fp32 sums of the same products: each within taps * 2^-24 of the sum of magnitudes
+    bound = gpu.cnn_conv2d_fwd(x.abs(), w.abs(), None, st, pd, 1, False, config=9) * (2 * C * R * R * 2.0 ** -24)
+    for cfg in _configs(gpu, "bf16 parts") + _configs(gpu, "direct"):
+        print(f"{shape} batch {batch} config {cfg}", flush=True)
+        for _ in range(2):
+            got = gpu.cnn_conv2d_fwd(x, w, None, st, pd, 1, False, config=cfg)
+            bad = int((~((got - want).abs() <= bound)).sum())
+            assert bad == 0, f"config {cfg}: {bad} of {got.numel()} outputs"
