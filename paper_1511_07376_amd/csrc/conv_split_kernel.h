@@ -2,8 +2,7 @@
 //
 // An fp32 value is the exact sum of three bf16 parts (bf16_split.h; 24
 // significant bits in three times 8, each part's rounding error passed on to
-// the next; exact for magnitudes from 2^-107 up, below which the third part
-// runs out of exponents and the absolute error is at most 2^-134).  A product of two values is
+// the next).  A product of two values is
 // then nine products of parts, of which the three below 2^-24 of the whole are
 // left out, and a v_mfma_f32_32x32x16_bf16 multiplies 16 taps in the time in
 // which the fp32 matrix instruction multiplies one (32 against 64 cycles for
@@ -11,17 +10,22 @@
 //
 // Accuracy: the leading products are summed in one fp32 accumulator (one
 // rounding per 16 taps) and the five smaller ones in a second, added at the
-// end.  Against 64-bit sums the error is 0.3 to 0.6 of the fp32 matrix
-// instruction's chain for 16 to 9216 taps of random values, signed or not
-// (1200 taps: 2.0e-7 against 6.2e-7 relative 2-norm).  With one accumulator,
+// end.  Against 64-bit sums the error is 0.3 to 0.9 of the fp32 matrix
+// instruction's chain for 2 to 4608 taps of random values, signed or not
+// (1200 taps: 0.4 to 0.8; a single tap: 1.02 to 1.03, for the products left
+// out).  With one accumulator,
 // or with truncated parts, it is larger than the chain's for some signs.
 //
-// Infinities, NaN and the end of the range: an infinite value has a NaN second
-// part, a finite one that rounds to an infinite first part an infinite second
-// part of the other sign, and the leading products of finite values can
-// overflow where their sum does not (their parts round up).  Every such sum
-// comes out as infinity or NaN; a sum that does is computed again in plain fp32
-// (repair_sums), which gives what the fp32 kernel gives.
+// What the parts cannot do is done again on the fp32 matrix cores, by the
+// waves whose sums it concerns (fp32_sums):
+// - An infinite value has a NaN second part, a finite one that rounds to an
+//   infinite first part an infinite second part of the other sign, and the
+//   leading products of finite values can overflow where their sum does not
+//   (their parts round up).  Every such sum comes out as infinity or NaN, and
+//   all sums that do are replaced.
+// - The parts of some magnitudes below 2^-107 do not add up to the value.  A
+//   workgroup that meets one (one instruction a pair of operands tells)
+//   replaces all its sums.
 //
 // The split is done once per loaded element, as it is stored to LDS, in steps
 // of a few vector instructions between the matrix-core instructions of the
@@ -67,52 +71,76 @@ __device__ inline void put_quad(unsigned short* tile, int step, int row, int qua
         *reinterpret_cast<uint2*>(tile + tile_at<ROWS>(step, q, row, quad >> 1) + (quad & 1) * 4) = make_uint2(a[q], b[q]);
 }
 
-// Replaces the sums of a wave's FM x FN blocks that are not finite by the plain
-// fp32 sums of the same taps (see the header comment).  Arguments as of
-// store_blocks.  A column of sums shares its pixel's window, read once per tap.
+// Replaces a wave's FM x FN blocks of sums, all or those that are not finite,
+// by sums of the same taps on the fp32 matrix cores (see the header comment).
+// kr: this lane's channel (matrix row) of the first block; off, ok: as of
+// store_blocks.
 template <int FM, int FN>
-__device__ inline void repair_sums(const ConvParams& p, floatx16 (&acc)[FM][FN], int g, int kr0, int half,
-                                   const int (&off)[FN], const bool (&ok)[FN], int kbeg, int klen) {
+__device__ inline void fp32_sums(const ConvParams& p, floatx16 (&acc)[FM][FN], bool all, int g, int kr, int half,
+                                 const int (&off)[FN], const bool (&ok)[FN], int kbeg, int klen) {
+    float nan = 0.0f;  // NaN if a sum is not finite
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) nan = __builtin_fmaf(acc[i][j][v], 0.0f, nan);
+    if (!all && !__any(nan != nan)) return;
+    const __amdgpu_buffer_rsrc_t xres =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.x), (short)0, p.xbytes, 0x00020000);
+    const __amdgpu_buffer_rsrc_t wres =
+        __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p.w), (short)0, p.wbytes, 0x00020000);
+    int h0[FN], w0[FN], img[FN];  // window corner and image group of this lane's pixels
 #pragma unroll
     for (int j = 0; j < FN; ++j) {
-        float nan = 0.0f;  // NaN if any sum of the column is not finite
+        const int n = off[j] / (p.K * p.PQ), pq = off[j] - n * p.K * p.PQ;
+        const int pp = (int)fdiv(pq, p.f_q);
+        h0[j] = pp * p.sh - p.ph;
+        w0[j] = (pq - pp * p.Q) * p.sw - p.pw;
+        img[j] = (n * p.C + g * p.Cg) * p.HW;
+    }
+    floatx16 sum[FM][FN];
+#pragma unroll
+    for (int i = 0; i < FM; ++i)
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) sum[i][j][v] = 0.0f;
+#pragma unroll 4
+    for (int k = half; k < klen + half; k += 2) {  // half: the k index of the instruction
+        const int c = (int)fdiv(kbeg + k, p.f_rs);
+        const int rs = kbeg + k - c * p.RS;
+        const int r = (int)fdiv(rs, p.f_s), s = rs - r * p.S;
+        float x[FN], w[FM];
+#pragma unroll
+        for (int j = 0; j < FN; ++j) {
+            const int h = h0[j] + r, c0 = w0[j] + s;
+            const bool in = ok[j] && k < klen && (unsigned)h < (unsigned)p.H && (unsigned)c0 < (unsigned)p.W;
+            const int at = in ? (img[j] + c * p.HW + h * p.W + c0) * 4 : kOutOfRange;
+            x[j] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(xres, at, 0, 0));
+            if (p.relu_x) x[j] = x[j] > 0.0f ? x[j] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < FM; ++i) {
+            const bool in = k < klen && kr + i * 32 < p.Kg;
+            const int at = in ? ((g * p.Kg + kr + i * 32) * p.Kr + kbeg + k) * 4 : kOutOfRange;
+            w[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(wres, at, 0, 0));
+        }
 #pragma unroll
         for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) nan = __builtin_fmaf(acc[i][j][v], 0.0f, nan);
-        if (!ok[j] || nan == 0.0f) continue;
-        const int n = off[j] / (p.K * p.PQ), pq = off[j] - n * p.K * p.PQ;
-        const int pp = (int)fdiv(pq, p.f_q);
-        const int h0 = pp * p.sh - p.ph, w0 = (pq - pp * p.Q) * p.sw - p.pw;
-        const float* xg = p.x + (size_t)(n * p.C + g * p.Cg) * p.HW;
-        const float* wg = p.w + (size_t)g * p.Kg * p.Kr;
+            for (int j = 0; j < FN; ++j)
+                sum[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(w[i], x[j], sum[i][j], 0, 0, 0);
+    }
 #pragma unroll
-        for (int i = 0; i < FM; ++i) {
-            const int kr = kr0 + i * 32 + 4 * half;  // of sum v: kr + 8 (v / 4) + v % 4
-            float sum[16];
+    for (int i = 0; i < FM; ++i)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) sum[v] = 0.0f;
-            for (int kk = kbeg; kk < kbeg + klen; ++kk) {
-                const int c = (int)fdiv(kk, p.f_rs);
-                const int rs = kk - c * p.RS;
-                const int r = (int)fdiv(rs, p.f_s);
-                const int h = h0 + r, w = w0 + rs - r * p.S;
-                const bool inside = (unsigned)h < (unsigned)p.H && (unsigned)w < (unsigned)p.W;
-                float xv = inside ? xg[(size_t)c * p.HW + h * p.W + w] : 0.0f;
-                if (p.relu_x) xv = xv > 0.0f ? xv : 0.0f;
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {  // rows past the group: its last one, not stored
-                    const int row = min(kr + 8 * (v / 4) + v % 4, p.Kg - 1);
-                    sum[v] = __builtin_fmaf(xv, wg[(size_t)row * p.Kr + kk], sum[v]);
-                }
-            }
+        for (int j = 0; j < FN; ++j)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const bool finite = __builtin_fabsf(acc[i][j][v]) <= 3.402823466e38f;
-                acc[i][j][v] = finite ? acc[i][j][v] : sum[v];
+                const bool keep = !all && __builtin_fabsf(acc[i][j][v]) <= 3.402823466e38f;
+                acc[i][j][v] = keep ? acc[i][j][v] : sum[i][j][v];
             }
-        }
-    }
 }
 
 // Bias, ReLU and NCHW store (lanes = consecutive pixels) of a wave's FM x FN
@@ -174,6 +202,8 @@ conv2d_split_f32(ConvParams p) {
     // [step][part][row][16 taps] in bf16 (see tile_at)
     constexpr int A_ELEMS = STEPS * 3 * AROWS * 16, B_ELEMS = STEPS * 3 * TN * 16;
     __shared__ __attribute__((aligned(16))) unsigned short smem[2 * (A_ELEMS + B_ELEMS)];
+    __shared__ int any_lost;  // an operand of the workgroup did not split
+    if (threadIdx.x == 0) any_lost = 0;
 
     const int tid = threadIdx.x;
     auto sA = [&](int buf) { return smem + buf * A_ELEMS; };
@@ -379,6 +409,7 @@ conv2d_split_f32(ConvParams p) {
     // weights') and stores the parts of a quad or oct once its last pair is done.
     constexpr int XPAIRS = KRUN / 2, PAIRS = XPAIRS + 2 * WV, SIDE = 3 * PAIRS;
     unsigned part[PAIRS][3];
+    unsigned lost = 0;  // whether an operand did not split (note_lost)
     auto side_step = [&](auto relu, int buf, int sg, int step) {
         const int i = step / 3, q = step % 3;
         float* v = i < XPAIRS ? &xr[sg][2 * i] : &wr[sg][2 * (i - XPAIRS)];
@@ -387,6 +418,7 @@ conv2d_split_f32(ConvParams p) {
                 v[0] = v[0] > 0.0f ? v[0] : 0.0f;
                 v[1] = v[1] > 0.0f ? v[1] : 0.0f;
             }
+        if (q == 2) note_lost(lost, v);
         part[i][q] = split_step(v, q < 2);
         if (q < 2) return;
         if (i >= XPAIRS) {
@@ -481,9 +513,9 @@ conv2d_split_f32(ConvParams p) {
 #pragma unroll
         for (int t = 0; t < SIDE; ++t) side_step(relu, buf, sg, t);
     };
-#pragma unroll
-    for (int j = 0; j < ST; ++j) load(j * BK, j);
     auto reduce = [&](auto relu) {
+#pragma unroll
+        for (int j = 0; j < ST; ++j) load(j * BK, j);
         store(relu, 0, 0);
         int it = 0;
         for (; it + ST - 1 < niter; it += ST) {
@@ -522,6 +554,7 @@ conv2d_split_f32(ConvParams p) {
     };
     if (p.relu_x) reduce(std::true_type{});
     else reduce(std::false_type{});
+    if (split_lost(lost)) any_lost = 1;
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
@@ -539,7 +572,8 @@ conv2d_split_f32(ConvParams p) {
         off[j] = ok[j] ? n * p.K * p.PQ + mc - n * p.PQ : 0;
     }
     const int kr0 = k0 + wm * FM * 32;
-    repair_sums<FM, FN>(p, acc, g, kr0, half, off, ok, kbeg, klen);
+    __syncthreads();
+    fp32_sums<FM, FN>(p, acc, any_lost != 0, g, kr0 + l32, half, off, ok, kbeg, klen);
     store_blocks<FM, FN>(p, acc, g, kr0, half, off, ok);
 }
 

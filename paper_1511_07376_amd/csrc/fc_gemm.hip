@@ -362,6 +362,9 @@ __global__ void __launch_bounds__(64 * KW) fc_direct_f32(FcParams p) {
 // splits them in its registers, so the loop has neither LDS nor barriers.  The
 // loads need 4-byte alignment only: the one chunk that may end inside (the
 // matrix's last) is loaded tap by tap.
+// What the parts cannot do is done again in fp32: by a wave, its run on the fp32
+// matrix cores where it met an operand whose parts do not add up to it (some
+// below 2^-107); sums that are not finite, one by one.
 template <int NB, int KW, bool RELU_X>
 __global__ void __launch_bounds__(64 * KW) fc_parts_f32(FcParams p) {
     constexpr int Q = 4;  // float4 loads per row and chunk (32 taps)
@@ -404,7 +407,8 @@ __global__ void __launch_bounds__(64 * KW) fc_parts_f32(FcParams p) {
                     f32x4, __builtin_amdgcn_raw_buffer_load_b128(xres, row + nb * block + 32 * q, soff, 0));
         }
     };
-    auto parts = [](f32x4 u, f32x4 v, bool relu, bf16x8* out) {
+    unsigned lost = 0;  // whether an operand did not split (note_lost)
+    auto parts = [&](f32x4 u, f32x4 v, bool relu, bf16x8* out) {
         float t[8] = {u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
         typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
         u32x4 w[3];
@@ -414,7 +418,10 @@ __global__ void __launch_bounds__(64 * KW) fc_parts_f32(FcParams p) {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int q = 0; q < 3; ++q) w[q][e] = split_step(t + 2 * e, q < 2);
+            for (int q = 0; q < 3; ++q) {
+                if (q == 2) note_lost(lost, t + 2 * e);
+                w[q][e] = split_step(t + 2 * e, q < 2);
+            }
 #pragma unroll
         for (int q = 0; q < 3; ++q) out[q] = __builtin_bit_cast(bf16x8, w[q]);
     };
@@ -447,7 +454,7 @@ __global__ void __launch_bounds__(64 * KW) fc_parts_f32(FcParams p) {
         if (c < nch) compute(0);
     }
     const int kt = kbase + nch * 32;  // a chunk that ends inside
-    if (kt < kend) {
+    auto load_tail = [&] {
 #pragma unroll
         for (int q = 0; q < Q; ++q)
 #pragma unroll
@@ -459,7 +466,30 @@ __global__ void __launch_bounds__(64 * KW) fc_parts_f32(FcParams p) {
                     xa[0][nb][q][e] = __builtin_bit_cast(
                         float, __builtin_amdgcn_raw_buffer_load_b32(xres, at < 0 ? at : at + nb * block, 0, 0));
             }
+    };
+    if (kt < kend) {
+        load_tail();
         compute(0);
+    }
+    if (__any(split_lost(lost))) {
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[nb][v] = low[nb][v] = 0.0f;
+        for (int c = 0; c < nch + (kt < kend); ++c) {
+            if (c < nch) load(c, 0);
+            else load_tail();
+#pragma unroll
+            for (int q = 0; q < Q; ++q)
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int nb = 0; nb < NB; ++nb) {
+                        const float xv = xa[0][nb][q][e];
+                        acc[nb] = __builtin_amdgcn_mfma_f32_32x32x2f32(RELU_X ? (xv > 0.0f ? xv : 0.0f) : xv,
+                                                                       wb[0][q][e], acc[nb], 0, 0, 0);
+                    }
+        }
     }
 
     // the waves' partial tiles, summed in wave order (lanes on consecutive words)

@@ -141,3 +141,23 @@ def test_strided_stems_every_output(gpu, shape, batch):
             got = gpu.cnn_conv2d_fwd(x, w, None, st, pd, 1, False, config=cfg)
             bad = int((~((got - want).abs() <= bound)).sum())
             assert bad == 0, f"config {cfg}: {bad} of {got.numel()} outputs"
+
+
+@pytest.mark.parametrize("xs,ws", [(-115, 0), (-120, 0), (-126, 0), (0, -120), (-140, 60), (-70, -50), (-60, -70)])
+def test_parts_of_small_values(gpu, xs, ws):
+    """Operands whose unscaled third part would lie below bfloat16's exponents,
+    subnormal operands, and results below 2^-126: against 64-bit sums no larger
+    an error than configuration 9's, beyond the 2^-150 of a subnormal result's
+    own rounding."""
+    x = wl.normal((2, 27, 9, 10), 1.0, 45, 0) * np.float32(2.0 ** xs)
+    w = (wl.normal((70, 27, 1, 1), 1.0, 45, 1).astype(np.float64) * 2.0 ** ws).astype(np.float32)
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double()).numpy()
+
+    def err(cfg):
+        y = to_host(gpu.cnn_conv2d_fwd(to_dev(x), to_dev(w), None, 1, 0, 1, False, config=cfg)).astype(np.float64)
+        return np.sqrt(np.mean((y - ref) ** 2))
+
+    fp32 = err(9)
+    for cfg in _configs(gpu, "bf16 parts"):
+        print(f"x 2^{xs} w 2^{ws} config {cfg}: {err(cfg):.3e} against {fp32:.3e}", flush=True)
+        assert err(cfg) <= 1.02 * fp32 + 2.0 ** -150, f"config {cfg}"

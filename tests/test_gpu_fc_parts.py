@@ -61,3 +61,32 @@ def test_fc_parts_no_less_accurate_than_fp32(gpu, I):
     for cfg in _configs(gpu):
         # 2^-25: the rounding of the result itself, which both have
         assert err(cfg) <= err(0) + 2.0 ** -25
+
+
+@pytest.mark.parametrize("xs,ws", [(-115, 0), (0, -120), (-140, 60), (-60, -70)])
+@pytest.mark.parametrize("I", [27, 333])
+def test_fc_parts_of_small_values(gpu, I, xs, ws):
+    """As test_parts_of_small_values of the convolutions, against the fp32 tiles."""
+    x = wl.normal((24, I), 1.0, 63, 0) * np.float32(2.0 ** xs)
+    w = (wl.normal((96, I), 1.0, 63, 1).astype(np.float64) * 2.0 ** ws).astype(np.float32)
+    ref = (torch.from_numpy(x).double() @ torch.from_numpy(w).double().t()).numpy()
+
+    def err(cfg):
+        y = to_host(gpu.cnn_fc_fwd(to_dev(x), to_dev(w), None, False, config=cfg)).astype(np.float64)
+        return np.sqrt(np.mean((y - ref) ** 2))
+
+    for cfg in _configs(gpu):
+        assert err(cfg) <= 1.02 * err(0) + 2.0 ** -150, f"config {cfg}"
+
+
+@pytest.mark.parametrize("sign", [1, -1])
+def test_fc_parts_just_inside_the_range(gpu, sign):
+    """Products and sums within 0.1% of the largest float, of inputs whose leading parts round up."""
+    for I, live in ((1, 1), (40, 16), (1100, 16)):
+        x = np.zeros((5, I), np.float32)
+        x[:, :live] = np.float32(1.998 * 2.0 ** 63 / live)
+        w = np.full((37, I), sign * 2.0 ** 64, np.float32)
+        ref = x.astype(np.float64) @ w.astype(np.float64).T
+        for cfg in [0] + _configs(gpu):
+            got = to_host(gpu.cnn_fc_fwd(to_dev(x), to_dev(w), None, False, config=cfg))
+            assert (np.abs(got - ref) <= live * 2.0 ** -23 * np.abs(ref)).all(), f"I {I} config {cfg}"
