@@ -25,14 +25,6 @@
 namespace cnn {
 namespace conv {
 
-// Window tap tables (LDS, one entry per tap of the chunk):
-//  kWindowNoPad:   byte offset of the tap within an image group; no padding.
-//  kWindowMask:    (byte offset << 5) | (r*S + s), tap index 31 past the
-//                  reduction; a 32-bit mask of the taps outside the image per pixel.
-//  kWindowAny:     two entries, byte offset and (r << 16) | s; bounds tested
-//                  per element (r = 0x7fff past the reduction).
-constexpr int kWindowNoPad = 0, kWindowMask = 1, kWindowAny = 2;
-
 template <int FM, int FN, int KW, bool VEC_W, int WINDOW>
 __global__ void __launch_bounds__(64 * KW)
 conv2d_direct_f32(ConvParams p) {

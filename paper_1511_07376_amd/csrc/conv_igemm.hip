@@ -76,9 +76,13 @@ void choose_splits(ConvParams& p, const ConvConfig& c) {
 
 
 // Whether a direct kernel's tap tables (two words a tap at most, the padding
-// of up to six rounds of the workgroup's waves included) fit the chunk.
+// of up to six rounds of the workgroup's waves included) fit the chunk, and the
+// filter and the image fit the packed rows and columns of kWindowAny: 15 and 16
+// bits, and row 0x7fff, which marks "past the reduction", outside the image from
+// the first window on.
 bool direct_fits(const ConvParams& p, const ConvConfig& c) {
-    return ceil_div(p.kchunk, 16) + 6 * (c.threads / 64) <= kDirectTableBytes / (16 * 8);
+    if (ceil_div(p.kchunk, 16) + 6 * (c.threads / 64) > kDirectTableBytes / (16 * 8)) return false;
+    return direct_window(p) != kWindowAny || (p.R <= 0x7fff && p.S <= 0xffff && p.H <= 0x7fff - p.ph);
 }
 
 // Estimated time (us) of a shape on a configuration, by which the families are
@@ -212,7 +216,7 @@ int conv_prepare(const ConvShape& s, int* cfg, ConvParams* out, int* per_launch)
     // fewer images: splitting it the same way is still correct).
     choose_splits(prm, kConfigs[*cfg]);
     if (kConfigs[*cfg].direct && !conv::direct_fits(prm, kConfigs[*cfg])) {
-        *cfg = 9;  // a reduction too long for the tap tables: the 64 x 64 tiles take it
+        *cfg = 9;  // a reduction or a filter beyond the tap tables: the 64 x 64 tiles take it
         choose_splits(prm, kConfigs[*cfg]);
     }
     return CNN_OK;

@@ -628,6 +628,17 @@ constexpr int kDirectStages = 2;  // 16-tap runs of loads in flight per wave
 // LDS the tap tables of a direct kernel may take; reductions that need more
 // are split further across workgroups.
 constexpr int kDirectTableBytes = 64 * 1024;
+// Window tap tables (LDS, one entry per tap of the chunk):
+//  kWindowNoPad:   byte offset of the tap within an image group; no padding.
+//  kWindowMask:    (byte offset << 5) | (r*S + s), tap index 31 past the
+//                  reduction; a 32-bit mask of the taps outside the image per pixel.
+//  kWindowAny:     two entries, byte offset and (r << 16) | s; bounds tested
+//                  per element (r = 0x7fff past the reduction).
+constexpr int kWindowNoPad = 0, kWindowMask = 1, kWindowAny = 2;
+inline int direct_window(const ConvParams& p) {
+    if (p.ph == 0 && p.pw == 0) return kWindowNoPad;
+    return p.RS <= 31 && (int64_t)p.Cg * p.HW * 4 < ((int64_t)1 << 27) ? kWindowMask : kWindowAny;
+}
 
 #define CNN_CONV_DECLARE(I, ...) int launch_c##I(const ConvParams& prm, bool vec_w, hipStream_t st);
 CNN_CONV_CONFIGS(CNN_CONV_DECLARE)

@@ -161,3 +161,34 @@ def test_parts_of_small_values(gpu, xs, ws):
     for cfg in _configs(gpu, "bf16 parts"):
         print(f"x 2^{xs} w 2^{ws} config {cfg}: {err(cfg):.3e} against {fp32:.3e}", flush=True)
         assert err(cfg) <= 1.02 * fp32 + 2.0 ** -150, f"config {cfg}"
+
+
+@pytest.mark.parametrize("H", [32765, 32766, 32767, 32770])
+def test_direct_rows_at_the_table_limit(gpu, H):
+    """A padded filter of 40 taps (rows and columns packed in a word) on images
+    around 32767 rows, infinite in the last ones: taps past the reduction must
+    read none of them."""
+    x = wl.normal((1, 1, H, 5), 1.0, 46, 0)
+    x[0, 0, 32764:] = np.inf
+    w = np.abs(wl.normal((33, 1, 8, 5), 1.0, 46, 1)) + np.float32(0.1)
+    ref = torch.nn.functional.conv2d(torch.from_numpy(x).double(), torch.from_numpy(w).double(), padding=1).numpy()
+    for cfg in [9] + _configs(gpu, "direct"):
+        print(f"H {H} config {cfg}", flush=True)
+        got = to_host(gpu.cnn_conv2d_fwd(to_dev(x), to_dev(w), None, 1, 1, 1, False, config=cfg))
+        inf = np.isinf(ref)
+        np.testing.assert_array_equal(np.isposinf(got), inf, err_msg=f"config {cfg}")
+        assert_gemm_close(np.where(inf, 0, got), np.where(inf, 0, ref), 40, f"config {cfg}")
+
+
+@pytest.mark.parametrize("R,S", [(32767, 1), (32768, 1), (33000, 1), (1, 65535), (1, 65536), (1, 66000)])
+def test_direct_filters_at_the_table_limit(gpu, R, S):
+    """Long one-dimensional filters, split until the tap tables hold a chunk:
+    the tables pack 15 bits of row and 16 of column."""
+    ph, pw = (1, 0) if S == 1 else (0, 1)
+    x = wl.normal((1, 1, R + 5 if S == 1 else 2, S + 5 if R == 1 else 2), 1.0, 47, 0)
+    w = wl.normal((33, 1, R, S), 1.0, 47, 1)
+    ref = oracle.conv2d_fwd(x, w, None, (1, 1), (ph, pw), 1, False)
+    for cfg in [9] + _configs(gpu, "direct"):
+        print(f"{R}x{S} config {cfg}", flush=True)
+        got = to_host(gpu.cnn_conv2d_fwd(to_dev(x), to_dev(w), None, 1, (ph, pw), 1, False, config=cfg))
+        assert_gemm_close(got, ref, R * S, f"config {cfg}")
