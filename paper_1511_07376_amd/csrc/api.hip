@@ -161,6 +161,8 @@ struct Plan {
                            // output must start as the bias)
     size_t split_off;      // may_split, not last: byte offset of its output in
                            // the split-output area of the workspace
+    int heuristic;         // CONV: the heuristic's configuration if the launch
+                           // will use it, or -1
     ConvShape conv;
     PoolShape pool;
 };
@@ -230,11 +232,10 @@ int plan_net(const cnn_layer_desc* L, int n, int N, int C, int H, int W, Plan* p
                     // any conv that some configuration splits; used when the
                     // configuration the launch will use (known unless it is still to
                     // be tuned) splits
-                    for (int cfg = 0; cfg < conv2d_num_configs() && !p.may_split; ++cfg)
-                        p.may_split = conv2d_splits(p.conv, cfg) > 1;
-                    const int cfg = conv2d_planned_config(p.conv, no_tune);
-                    p.split = cfg != -2 && conv2d_splits(p.conv, cfg) > 1;
-                    p.may_split = p.may_split || p.split;
+                    const ConvPlan plan = conv2d_plan(p.conv, conv2d_planned_config(p.conv, no_tune));
+                    p.split = plan.split;
+                    p.may_split = plan.may_split;
+                    p.heuristic = plan.heuristic;
                 }
                 break;
             }
@@ -466,6 +467,7 @@ int run_net(const cnn_layer_desc* L, int n, const float* x, int N, int C, int H,
             case CNN_LAYER_CONV: {
                 ConvOpts o;
                 o.no_tune = no_tune;
+                o.planned = p.heuristic;
                 o.relu_in = relu_in;
                 o.prefilled = p.split;
                 o.relu_left = relu_left;

@@ -63,8 +63,7 @@ struct FastDiv {
 };
 inline FastDiv make_fastdiv(unsigned d) {
     if (d == 0) d = 1;
-    unsigned l = 0;
-    while ((1u << l) < d) ++l;
+    const unsigned l = d > 1 ? 32 - __builtin_clz(d - 1) : 0;
     const uint64_t m = ((((uint64_t)1 << l) - d) << 32) / d + 1;
     return FastDiv{(unsigned)m, l};
 }
@@ -99,12 +98,15 @@ int pool_out(int H, int W, int kh, int kw, int sh, int sw, int ph, int pw, int c
 //             reduction) is skipped and *relu_left set, for the consumer.
 //   no_tune   never run the auto-tuner for this call (a shape without a
 //             record takes the heuristic), as for a caller that must not
-//             allocate or synchronise.
+//             allocate or synchronise;
+//   planned   the heuristic's configuration where the caller has it already
+//             (conv2d_plan), for a shape without a record.
 struct ConvOpts {
     bool relu_in = false;
     bool prefilled = false;
     bool* relu_left = nullptr;
     bool no_tune = false;
+    int planned = -1;
 };
 // cfg: index into the convolution configuration table, or -1 for the
 // built-in heuristic.
@@ -112,8 +114,14 @@ int launch_conv2d(const ConvShape& s, const float* x, const float* w, const floa
                   int relu, float* y, hipStream_t st, int cfg, const ConvOpts* opt = nullptr);
 int conv2d_num_configs();
 const char* conv2d_config_name(int i);
-// Reduction splits configuration cfg (-1: heuristic) uses for this shape.
-int conv2d_splits(const ConvShape& s, int cfg);
+// What a network's plan needs to know of a convolution with the configuration
+// cfg (-1: heuristic, -2: still to be tuned): whether that splits the reduction,
+// whether any configuration does, and the heuristic's choice (-1 unless cfg is).
+struct ConvPlan {
+    bool split, may_split;
+    int heuristic;
+};
+ConvPlan conv2d_plan(const ConvShape& s, int cfg);
 // The built-in heuristic's configuration for this shape (-1 if none applies).
 int conv2d_heuristic_config(const ConvShape& s);
 // Convolution with the tuned configuration for this shape (auto-tuning it

@@ -26,7 +26,7 @@ struct ConvConfig {
 #define CNN_DIRECT_ENTRY(I, FM, FN, KW) \
     ConvConfig{"direct, " #FM "x" #FN " blocks, " #KW " waves", FM * 32, FN * 32, 16, 64 * KW, true, &launch_c##I},
 
-const ConvConfig kConfigs[] = {
+constexpr ConvConfig kConfigs[] = {
     CNN_CONV_CONFIGS(CNN_CONV_ENTRY) CNN_SPLIT_CONFIGS(CNN_SPLIT_ENTRY) CNN_DIRECT_CONFIGS(CNN_DIRECT_ENTRY)};
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
 
@@ -61,7 +61,10 @@ constexpr int kSplitBelowTiles = 384, kSplitTarget = 1024;
 // with at least four 16-tap runs a wave: at 112 tiles (512 x 14 x 14, 3x3, one
 // image) two to nine chunks measured no faster than one.
 constexpr int kDirectSplitBelow = 64, kDirectTarget = 256;
-void choose_splits(ConvParams& p, const ConvConfig& c) {
+struct Chunks {
+    int splits, kchunk;
+};
+__attribute__((always_inline)) inline Chunks chunks_of(const ConvParams& p, const ConvConfig& c) {
     const int tiles = ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G;
     const int nslab = ceil_div(p.Kr, c.bk);
     int splits = 1;
@@ -69,19 +72,23 @@ void choose_splits(ConvParams& p, const ConvConfig& c) {
         if (tiles <= kDirectSplitBelow)
             splits = std::max(1, std::min(ceil_div(kDirectTarget, tiles), nslab / (c.threads / 64 * 4)));
     } else if (tiles <= kSplitBelowTiles) splits = std::max(1, std::min(ceil_div(kSplitTarget, tiles), nslab / 8));
-    const int slabs_per_chunk = ceil_div(nslab, splits);
-    p.kchunk = splits > 1 ? slabs_per_chunk * c.bk : p.Kr;
-    p.splits = splits > 1 ? ceil_div(p.Kr, p.kchunk) : 1;
+    if (splits == 1) return {1, p.Kr};
+    const int kchunk = ceil_div(nslab, splits) * c.bk;
+    return {ceil_div(p.Kr, kchunk), kchunk};
 }
-
+void choose_splits(ConvParams& p, const ConvConfig& c) {
+    const Chunks k = chunks_of(p, c);
+    p.splits = k.splits;
+    p.kchunk = k.kchunk;
+}
 
 // Whether a direct kernel's tap tables (two words a tap at most, the padding
 // of up to six rounds of the workgroup's waves included) fit the chunk, and the
 // filter and the image fit the packed rows and columns of kWindowAny: 15 and 16
 // bits, and row 0x7fff, which marks "past the reduction", outside the image from
 // the first window on.
-bool direct_fits(const ConvParams& p, const ConvConfig& c) {
-    if (ceil_div(p.kchunk, 16) + 6 * (c.threads / 64) > kDirectTableBytes / (16 * 8)) return false;
+__attribute__((always_inline)) inline bool direct_fits(const ConvParams& p, int kchunk, const ConvConfig& c) {
+    if (ceil_div(kchunk, 16) + 6 * (c.threads / 64) > kDirectTableBytes / (16 * 8)) return false;
     return direct_window(p) != kWindowAny || (p.R <= 0x7fff && p.S <= 0xffff && p.H <= 0x7fff - p.ph);
 }
 
@@ -98,14 +105,14 @@ bool direct_fits(const ConvParams& p, const ConvConfig& c) {
 struct TimeModel {
     double base, extra, odd, strided, mask, scalar, out;  // of a family
 };
-const TimeModel kFp32Model = {4.13, 1.71, 0.999, 1.1, 1.03, 1.31, 0.163}, kSplitModel = {5.04, 1.97, 1.11, 1.07, 1.04, 1.39, 0.352},
+constexpr TimeModel kFp32Model = {4.13, 1.71, 0.999, 1.1, 1.03, 1.31, 0.163}, kSplitModel = {5.04, 1.97, 1.11, 1.07, 1.04, 1.39, 0.352},
                 kDirectModel = {3.76, 0.623, 1.45, 1.23, 1.03, 1.24, 0.143};
 // Per slab of one workgroup (us): latency alone, throughput share.
 struct SlabTime {
     int cfg;
     double latency, share;
 };
-const SlabTime kSlabTimes[] = {
+constexpr SlabTime kSlabTimes[] = {
     {0, 0.509, 1.14},
     {2, 0.483, 0.486},
     {4, 0.503, 0.52},
@@ -124,24 +131,43 @@ const SlabTime kSlabTimes[] = {
     {24, 0.821, 0.666},
 };
 
-double estimate(ConvParams p, int cfg) {
-    const ConvConfig& c = kConfigs[cfg];
-    choose_splits(p, c);
-    const TimeModel& f = c.direct ? kDirectModel : cfg >= 16 ? kSplitModel : kFp32Model;
+constexpr SlabTime slab_time(int cfg) {
     const SlabTime* t = kSlabTimes;
     while (t->cfg != cfg) ++t;
-    const int64_t wgs = (int64_t)ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G * p.splits;
-    const double queue = (double)ceil_div64(wgs, 256);
-    int slabs = ceil_div(p.kchunk, c.bk);
+    return *t;
+}
+
+// A call evaluates ten of these: with the configuration known at compile time
+// its divisions become shifts, and the ten take 95 ns (470 with a loop over the
+// table).
+template <int CFG>
+double estimate(const ConvParams& p, const Chunks& k) {
+    constexpr ConvConfig c = kConfigs[CFG];
+    constexpr TimeModel f = c.direct ? kDirectModel : CFG >= 16 ? kSplitModel : kFp32Model;
+    constexpr SlabTime t = slab_time(CFG);
+    const int64_t wgs = (int64_t)ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G * k.splits;
+    const double queue = (double)(int)ceil_div64(wgs, 256);
+    int slabs = ceil_div(k.kchunk, c.bk);
     if (c.direct) slabs = ceil_div(slabs, c.threads / 64);
     double scale = p.Kr % 4 ? f.odd : 1.0;
     const bool padded = p.ph > 0 || p.pw > 0;
     if (p.sw > 1 && (!padded || p.RS <= 63)) scale *= f.strided;
     else if (padded) scale *= p.RS <= 31 ? f.mask : f.scalar;
-    const double mout = 1e-6 * (double)p.M * p.K;
-    double us = f.base + (slabs + f.extra) * std::max(t->latency, queue * t->share) * scale + 4.0 * f.out * mout;
-    if (p.splits > 1) us += 6.06 + 3.4 * p.splits * mout;
+    const double mout = 1e-6 * ((double)p.M * p.K);
+    double us = f.base + (slabs + f.extra) * std::max(t.latency, queue * t.share) * scale + 4.0 * f.out * mout;
+    if (k.splits > 1) us += 6.06 + 3.4 * k.splits * mout;
     return us;
+}
+double estimate_fp32(const ConvParams& p, int cfg) {
+    switch (cfg) {  // every choice of fp32_config
+        case 0: return estimate<0>(p, chunks_of(p, kConfigs[0]));
+        case 2: return estimate<2>(p, chunks_of(p, kConfigs[2]));
+        case 4: return estimate<4>(p, chunks_of(p, kConfigs[4]));
+        case 6: return estimate<6>(p, chunks_of(p, kConfigs[6]));
+        case 8: return estimate<8>(p, chunks_of(p, kConfigs[8]));
+        case 9: return estimate<9>(p, chunks_of(p, kConfigs[9]));
+        default: return estimate<10>(p, chunks_of(p, kConfigs[10]));
+    }
 }
 
 // The configuration of a shape when no tuned entry exists: the fp32 one unless
@@ -150,19 +176,24 @@ double estimate(ConvParams p, int cfg) {
 // of the split kernels, any direct one: 15%; over the 460 shapes 5 then ran
 // more than 5% slower than on the fp32 choice, against 23 without).
 constexpr double kMargin = 1.15;
-int heuristic_config(const ConvParams& p0, int G) {
-    int best = fp32_config(p0, G);
-    double least = estimate(p0, best);
-    for (int cfg = 16; cfg < kNumConfigs; ++cfg) {
-        ConvParams p = p0;
-        choose_splits(p, kConfigs[cfg]);
-        if (kConfigs[cfg].direct && !direct_fits(p, kConfigs[cfg])) continue;
-        const double us = estimate(p0, cfg) * (kConfigs[cfg].direct || p.splits > 1 ? kMargin : 1.0);
-        if (us < least) {
-            least = us;
-            best = cfg;
-        }
+template <int CFG>
+__attribute__((always_inline)) inline void consider(const ConvParams& p, int* best, double* least) {
+    constexpr ConvConfig c = kConfigs[CFG];
+    const Chunks k = chunks_of(p, c);
+    if (c.direct && !direct_fits(p, k.kchunk, c)) return;
+    const double us = estimate<CFG>(p, k) * (c.direct || k.splits > 1 ? kMargin : 1.0);
+    if (us < *least) {
+        *least = us;
+        *best = CFG;
     }
+}
+int heuristic_config(const ConvParams& p, int G) {
+    int best = fp32_config(p, G);
+    double least = estimate_fp32(p, best);
+#define CNN_CONSIDER(I, ...) consider<I>(p, &best, &least);
+    CNN_SPLIT_CONFIGS(CNN_CONSIDER)
+    CNN_DIRECT_CONFIGS(CNN_CONSIDER)
+#undef CNN_CONSIDER
     return best;
 }
 
@@ -215,7 +246,7 @@ int conv_prepare(const ConvShape& s, int* cfg, ConvParams* out, int* per_launch)
     // One split decision for every launch of the call (the last one may hold
     // fewer images: splitting it the same way is still correct).
     choose_splits(prm, kConfigs[*cfg]);
-    if (kConfigs[*cfg].direct && !conv::direct_fits(prm, kConfigs[*cfg])) {
+    if (kConfigs[*cfg].direct && !conv::direct_fits(prm, prm.kchunk, kConfigs[*cfg])) {
         *cfg = 9;  // a reduction or a filter beyond the tap tables: the 64 x 64 tiles take it
         choose_splits(prm, kConfigs[*cfg]);
     }
@@ -230,11 +261,16 @@ int conv2d_heuristic_config(const ConvShape& s) {
     return conv_prepare(s, &cfg, &prm, &per_launch) == CNN_OK ? cfg : -1;
 }
 
-int conv2d_splits(const ConvShape& s, int cfg) {
+ConvPlan conv2d_plan(const ConvShape& s, int cfg) {
+    ConvPlan plan = {false, false, -1};
     ConvParams prm;
-    int per_launch;
-    if (conv_prepare(s, &cfg, &prm, &per_launch) != CNN_OK) return 1;
-    return prm.splits;
+    int per_launch, used = cfg == -2 ? 0 : cfg;
+    if (conv_prepare(s, &used, &prm, &per_launch) != CNN_OK) return plan;
+    plan.split = cfg != -2 && prm.splits > 1;
+    if (cfg == -1) plan.heuristic = used;
+    plan.may_split = plan.split;
+    for (int c = 0; c < kNumConfigs && !plan.may_split; ++c) plan.may_split = conv::chunks_of(prm, kConfigs[c]).splits > 1;
+    return plan;
 }
 
 int launch_conv2d(const ConvShape& s, const float* x, const float* w, const float* bias, int relu,

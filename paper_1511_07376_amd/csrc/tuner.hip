@@ -140,6 +140,7 @@ int conv2d_dispatch(const ConvShape& s, const float* x, const float* w, const fl
             g_table[key_of(s)] = cfg;
         }
     }
+    if (cfg < 0 && opt) cfg = opt->planned;
     return launch_conv2d(s, x, w, bias, relu, y, st, cfg, opt);
 }
 
