@@ -92,43 +92,52 @@ __attribute__((always_inline)) inline bool direct_fits(const ConvParams& p, int 
     return direct_window(p) != kWindowAny || (p.R <= 0x7fff && p.S <= 0xffff && p.H <= 0x7fff - p.ph);
 }
 
-// Estimated time (us) of a shape on a configuration, by which the families are
+// Estimated time (us) of a call on a configuration, by which the families are
 // compared: a start of `base`, then per slab the larger of the latency of one
 // workgroup alone and the throughput time of those that share a compute unit,
-// scaled by the gather's mode, plus the output's bytes, plus the fill, the
-// ReLU pass and the atomics of a split reduction.  The constants were fitted
-// to measured times of every configuration on 460 shapes (AlexNet's, LeNet's,
-// CIFAR-10 quick's and the sweep's layers at batches 1 to 256, and 350 random
-// ones of 7 to 227 pixels, 3 to 512 channels, filters 1x1 to 11x11, strides 1
-// to 4, reductions of 3 to 60000 taps).  The choice by these estimates came
-// within 3.5% (geometric mean) of always taking the fastest.
+// scaled by the way the operands are read, plus the output's bytes, plus the
+// fill, the ReLU pass and the atomics of a split reduction.  Weight rows that
+// are not whole 16-byte vectors are read with 32-bit loads (`odd`), and rows
+// much longer than what the vector L1 keeps of them cost more per slab
+// (`longer`, up to 1024 taps, by the share of the tile's rows that exist).
+// The constants were fitted (least squares of the logarithms, weight on the
+// configurations near a shape's fastest) to times of calls through the Python
+// binding with configurations 16 to 24 and the fp32 choice on 2464 shapes:
+// AlexNet's, LeNet's, CIFAR-10 quick's and the sweep's layers at batches 1 to
+// 256, and random ones of 7 to 227 pixels, 3 to 512 channels, filters 1x1 to
+// 11x11, strides 1 to 4 (profiles/conv_choice_times.csv).  The residuals are 8
+// to 11%.
 struct TimeModel {
-    double base, extra, odd, strided, mask, scalar, out;  // of a family
+    double base, extra, mask, out, fill, sums;  // of a family
 };
-constexpr TimeModel kFp32Model = {4.13, 1.71, 0.999, 1.1, 1.03, 1.31, 0.163}, kSplitModel = {5.04, 1.97, 1.11, 1.07, 1.04, 1.39, 0.352},
-                kDirectModel = {3.76, 0.623, 1.45, 1.23, 1.03, 1.24, 0.143};
-// Per slab of one workgroup (us): latency alone, throughput share.
+constexpr TimeModel kFp32Model = {5.62, 0.464, 1.08, 0.243, 7.14, 1.12},
+                    kSplitModel = {5.41, 1.55, 1.02, 0.406, 5.51, 3.09},
+                    kDirectModel = {4.75, 0.303, 1.04, 0.34, 3.63, 4.54};
+// A call's least time: one launch, or those of a split reduction.
+constexpr double kLeastUs = 8.4, kLeastSplitUs = 14.0;
+// Per slab of one workgroup (us): latency alone, throughput share; scales of
+// the two for strided gathers; of both for the other ways to read operands.
 struct SlabTime {
     int cfg;
-    double latency, share;
+    double latency, share, strided_latency, strided_share, odd, any, longer, longer_odd;
 };
 constexpr SlabTime kSlabTimes[] = {
-    {0, 0.509, 1.14},
-    {2, 0.483, 0.486},
-    {4, 0.503, 0.52},
-    {6, 0.569, 0.785},
-    {8, 0.596, 0.284},
-    {9, 0.495, 0.269},
-    {10, 0.848, 0.525},
-    {16, 1.29, 0.626},
-    {17, 0.801, 0.345},
-    {18, 0.78, 0.34},
-    {19, 1.03, 0.542},
-    {20, 0.467, 0.203},
-    {21, 0.694, 0.48},
-    {22, 0.478, 0.382},
-    {23, 0.5, 0.762},
-    {24, 0.821, 0.666},
+    {0, 0.509, 0.995, 1.1, 1.07, 1.1, 1.31, 0, 0},
+    {2, 0.483, 0.493, 1.1, 1.19, 1.13, 1.16, 0, 0},
+    {4, 0.503, 0.487, 1.1, 1.2, 1.03, 1.24, 0, 0},
+    {6, 0.569, 0.756, 1.1, 1.08, 0.98, 1.29, 0.05, 0.0427},
+    {8, 0.326, 0.26, 1.29, 1.16, 0.936, 1.59, 0.0918, 0.18},
+    {9, 0.495, 0.226, 1.1, 1.19, 1.1, 1.23, 0.116, 0.0801},
+    {10, 0.602, 0.468, 1.36, 1.27, 1.13, 1.29, 0.0723, 0.0153},
+    {16, 1.19, 0.583, 1.28, 1.24, 1.17, 1.24, 0.0398, 0.0733},
+    {17, 0.654, 0.286, 1.33, 1.3, 1.24, 1.16, 0.216, 0.668},
+    {18, 0.666, 0.294, 1.31, 1.25, 1.07, 1.45, 0.251, 0.369},
+    {19, 0.959, 0.528, 1.38, 1.28, 1.16, 1.31, 0.035, 0.116},
+    {20, 0.32, 0.149, 1.56, 1.44, 1.2, 1.32, 0.46, 0.944},
+    {21, 0.572, 0.335, 1.39, 1.43, 1.22, 1.37, 0.326, 0.379},
+    {22, 0.307, 0.276, 1.24, 1.24, 1.45, 1.11, 0.226, 1.04},
+    {23, 0.5, 0.569, 1.25, 1.25, 1.34, 1.02, 0.146, 1.12},
+    {24, 0.705, 0.593, 1.26, 1.26, 1.28, 1.15, 0.022, 0.191},
 };
 
 constexpr SlabTime slab_time(int cfg) {
@@ -149,14 +158,17 @@ double estimate(const ConvParams& p, const Chunks& k) {
     const double queue = (double)(int)ceil_div64(wgs, 256);
     int slabs = ceil_div(k.kchunk, c.bk);
     if (c.direct) slabs = ceil_div(slabs, c.threads / 64);
-    double scale = p.Kr % 4 ? f.odd : 1.0;
+    const double rows = std::min(1.0, p.Kr * (1.0 / 1024)) * p.Kg / (ceil_div(p.Kg, c.tm) * c.tm);
+    const double reads = p.Kr % 4 ? t.odd + t.longer_odd * rows : 1.0 + t.longer * rows;
     const bool padded = p.ph > 0 || p.pw > 0;
-    if (p.sw > 1 && (!padded || p.RS <= 63)) scale *= f.strided;
-    else if (padded) scale *= p.RS <= 31 ? f.mask : f.scalar;
+    const double window = !padded ? 1.0 : p.RS <= 31 ? f.mask : t.any;
+    const bool strided = p.sw > 1 && (c.direct || !padded || p.RS <= 63);
+    const double scale = strided && !c.direct ? 1.0 : reads * window;
+    const double slab = std::max(t.latency * (strided ? t.strided_latency : 1.0),
+                                 queue * t.share * (strided ? t.strided_share : 1.0)) * scale;
     const double mout = 1e-6 * ((double)p.M * p.K);
-    double us = f.base + (slabs + f.extra) * std::max(t.latency, queue * t.share) * scale + 4.0 * f.out * mout;
-    if (k.splits > 1) us += 6.06 + 3.4 * k.splits * mout;
-    return us;
+    const double us = f.base + (slabs + f.extra) * slab + 4.0 * f.out * mout;
+    return k.splits > 1 ? std::max(kLeastSplitUs, us + f.fill + f.sums * k.splits * mout) : std::max(kLeastUs, us);
 }
 double estimate_fp32(const ConvParams& p, int cfg) {
     switch (cfg) {  // every choice of fp32_config
@@ -171,17 +183,24 @@ double estimate_fp32(const ConvParams& p, int cfg) {
 }
 
 // The configuration of a shape when no tuned entry exists: the fp32 one unless
-// a split or a direct one is estimated faster, the latter two by margins that
-// leave out the shapes where the estimate's error decides (a split reduction
-// of the split kernels, any direct one: 15%; over the 460 shapes 5 then ran
-// more than 5% slower than on the fp32 choice, against 23 without).
-constexpr double kMargin = 1.15;
+// a split or a direct one is estimated faster by a margin that leaves out the
+// shapes where the estimate's error decides: for up to five workgroups per
+// compute unit, where the last ones to run weigh most, the estimated gains were
+// 4% too large in the mean, beyond that 1.5% too small.  On 700 random shapes
+// that were not fitted to, the choice was 1.140 times as fast as the fp32 one
+// (the fastest configuration 1.167), with 12 shapes more than 3% slower than it;
+// the constants fitted on 460 shapes before gave 1.127 and 36.  Without margins,
+// 2824 shapes gave 1.144 and 111, with them 1.140 and 44.
+constexpr double kMargin = 1.06, kMarginManyWorkgroups = 1.01;
+constexpr double kMarginSplitOrDirect = 1.05;  // on top of it, for a split reduction or a direct kernel
 template <int CFG>
 __attribute__((always_inline)) inline void consider(const ConvParams& p, int* best, double* least) {
     constexpr ConvConfig c = kConfigs[CFG];
     const Chunks k = chunks_of(p, c);
     if (c.direct && !direct_fits(p, k.kchunk, c)) return;
-    const double us = estimate<CFG>(p, k) * (c.direct || k.splits > 1 ? kMargin : 1.0);
+    const int64_t wgs = (int64_t)ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G * k.splits;
+    double us = estimate<CFG>(p, k) * (wgs > 5 * 256 ? kMarginManyWorkgroups : kMargin);
+    if (c.direct || k.splits > 1) us *= kMarginSplitOrDirect;
     if (us < *least) {
         *least = us;
         *best = CFG;
@@ -190,6 +209,7 @@ __attribute__((always_inline)) inline void consider(const ConvParams& p, int* be
 int heuristic_config(const ConvParams& p, int G) {
     int best = fp32_config(p, G);
     double least = estimate_fp32(p, best);
+    if (least <= kLeastUs) return best;  // no other is estimated below kLeastUs
 #define CNN_CONSIDER(I, ...) consider<I>(p, &best, &least);
     CNN_SPLIT_CONFIGS(CNN_CONSIDER)
     CNN_DIRECT_CONFIGS(CNN_CONSIDER)
