@@ -122,6 +122,10 @@ struct ConvPlan {
     int heuristic;
 };
 ConvPlan conv2d_plan(const ConvShape& s, int cfg);
+// Whether the tuner may take configuration c for this shape: it runs as such
+// (cnn_conv2d_fwd_config runs another where a direct kernel's tables are too
+// small) and gives up no accuracy.
+bool conv2d_config_takes(const ConvShape& s, int c);
 // The built-in heuristic's configuration for this shape (-1 if none applies).
 int conv2d_heuristic_config(const ConvShape& s);
 // Convolution with the tuned configuration for this shape (auto-tuning it

@@ -29,6 +29,7 @@ struct ConvConfig {
 constexpr ConvConfig kConfigs[] = {
     CNN_CONV_CONFIGS(CNN_CONV_ENTRY) CNN_SPLIT_CONFIGS(CNN_SPLIT_ENTRY) CNN_DIRECT_CONFIGS(CNN_DIRECT_ENTRY)};
 constexpr int kNumConfigs = sizeof(kConfigs) / sizeof(kConfigs[0]);
+constexpr int kFirstSplit = 16;  // of the configurations on bf16 parts
 
 // The fp32 matrix-core configuration of a shape when no tuned entry exists,
 // fitted by hand to measured times of configurations 0 to 15 on AlexNet's, LeNet's and CIFAR-10 quick's
@@ -152,7 +153,7 @@ constexpr SlabTime slab_time(int cfg) {
 template <int CFG>
 double estimate(const ConvParams& p, const Chunks& k) {
     constexpr ConvConfig c = kConfigs[CFG];
-    constexpr TimeModel f = c.direct ? kDirectModel : CFG >= 16 ? kSplitModel : kFp32Model;
+    constexpr TimeModel f = c.direct ? kDirectModel : CFG >= kFirstSplit ? kSplitModel : kFp32Model;
     constexpr SlabTime t = slab_time(CFG);
     const int64_t wgs = (int64_t)ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G * k.splits;
     const double queue = (double)(int)ceil_div64(wgs, 256);
@@ -182,6 +183,11 @@ double estimate_fp32(const ConvParams& p, int cfg) {
     }
 }
 
+// The products of parts that the split kernels leave out make a sum of a single
+// tap 2 to 3% less accurate than its fp32 product, so neither the choice nor the
+// tuner takes them for one (from two taps on they are the more accurate).
+constexpr int kLeastSplitTaps = 2;
+
 // The configuration of a shape when no tuned entry exists: the fp32 one unless
 // a split or a direct one is estimated faster by a margin that leaves out the
 // shapes where the estimate's error decides: for up to five workgroups per
@@ -197,7 +203,7 @@ template <int CFG>
 __attribute__((always_inline)) inline void consider(const ConvParams& p, int* best, double* least) {
     constexpr ConvConfig c = kConfigs[CFG];
     const Chunks k = chunks_of(p, c);
-    if (c.direct && !direct_fits(p, k.kchunk, c)) return;
+    if (c.direct ? !direct_fits(p, k.kchunk, c) : p.Kr < kLeastSplitTaps) return;
     const int64_t wgs = (int64_t)ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G * k.splits;
     double us = estimate<CFG>(p, k) * (wgs > 5 * 256 ? kMarginManyWorkgroups : kMargin);
     if (c.direct || k.splits > 1) us *= kMarginSplitOrDirect;
@@ -274,6 +280,13 @@ int conv_prepare(const ConvShape& s, int* cfg, ConvParams* out, int* per_launch)
 }
 
 }  // namespace
+
+bool conv2d_config_takes(const ConvShape& s, int c) {
+    ConvParams prm;
+    int per_launch, cfg = c;
+    if (conv_prepare(s, &cfg, &prm, &per_launch) != CNN_OK || cfg != c) return false;
+    return kConfigs[c].direct || c < conv::kFirstSplit || prm.Kr >= conv::kLeastSplitTaps;
+}
 
 int conv2d_heuristic_config(const ConvShape& s) {
     ConvParams prm;

@@ -832,8 +832,9 @@ int fc_heuristic(int N, int I, int O, bool vec) {
     if (N <= kGemvMaxN) return 3;
     if (vec && N <= 64 && I <= 4096 && O <= (N <= 32 ? 2048 : 512)) return 2;
     const bool grid = (int64_t)ceil_div(O, 32) * ceil_div(N, 32) < (1 << 20);  // within a launch's limits
-    if (grid && I <= (N <= 32 ? 1000 : 768)) return 5;
-    if (grid && N <= 32 && !vec && O <= 2048) return 6;
+    // a single product is less accurate on parts (conv_split_kernel.h)
+    if (grid && I > 1 && I <= (N <= 32 ? 1000 : 768)) return 5;
+    if (grid && I > 1 && N <= 32 && !vec && O <= 2048) return 6;
     if (N > 32 && N <= 64 && O >= 2048 && I >= 4096) return 4;
     if (N <= 32) return 1;
     if (N > 64 && O <= 1024) return 1;

@@ -74,6 +74,7 @@ int tune(const ConvShape& s, const float* x, const float* w, const float* bias, 
     };
     std::vector<std::pair<float, int>> first;
     for (int c = 0; c < conv2d_num_configs(); ++c) {
+        if (!conv2d_config_takes(s, c)) continue;
         const float ms = time_cfg(c, kTimedRuns);
         if (ms >= 0.0f) first.emplace_back(ms, c);
     }

@@ -43,3 +43,22 @@ def test_split_and_direct_kernels_where_they_are_faster(shape, first, last):
 def test_launch_bound_calls_keep_the_fp32_tiles():
     for shape in ((2, 24, 18, 15, 118, 3, 3, 1, 0, 2), (1, 3, 9, 9, 16, 3, 3, 1, 0, 1), (2, 8, 79, 61, 20, 3, 3, 1, 1, 2)):
         assert choice(*shape) < FIRST_SPLIT
+
+
+@pytest.mark.parametrize("n", [1, 8, 64, 256])
+def test_sums_of_one_tap_stay_in_fp32(n):
+    """The split kernels are less accurate there; the direct ones are fp32."""
+    for c, groups in ((1, 1), (64, 64), (512, 512)):
+        for k in (512, 1024):
+            for h in (7, 56, 112):
+                if n * max(c, k) * h * h < 1 << 31:
+                    assert not FIRST_SPLIT <= choice(n, c, h, h, k, 1, 1, 1, 0, groups) < FIRST_DIRECT
+    takes = cnn.lib._ZN3cnn19conv2d_config_takesERKNS_9ConvShapeEi
+    takes.restype = ctypes.c_bool
+    one, two = ((ctypes.c_int * 14)(n, c, 14, 14, 64, 1, 1, 1, 1, 0, 0, 1, 14, 14) for c in (1, 2))
+    for cfg in range(cnn.cnn_conv2d_num_configs()):
+        assert takes(ctypes.byref(two), cfg)
+        assert takes(ctypes.byref(one), cfg) == (not FIRST_SPLIT <= cfg < FIRST_DIRECT)
+    # a reduction beyond the direct kernels' tap tables is not tuned under their names
+    long = (ctypes.c_int * 14)(16, 1024, 15, 15, 60, 3, 3, 1, 1, 1, 1, 1, 15, 15)
+    assert [takes(ctypes.byref(long), cfg) for cfg in range(FIRST_DIRECT, cnn.cnn_conv2d_num_configs())] == [False] * 3

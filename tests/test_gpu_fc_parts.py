@@ -49,7 +49,7 @@ def test_fc_parts_values_that_do_not_split(gpu, I):
         assert np.abs(got[fin] - want[fin]).max() <= 2 * I * 2.0 ** -24 * 8 * I
 
 
-@pytest.mark.parametrize("I", [6, 333, 4000])
+@pytest.mark.parametrize("I", [2, 6, 333, 4000])
 def test_fc_parts_no_less_accurate_than_fp32(gpu, I):
     x, w = wl.normal((24, I), 1.0, 62, 0), wl.normal((96, I), 1.0, 62, 1)
     ref = (torch.from_numpy(x).double() @ torch.from_numpy(w).double().t()).numpy()
@@ -59,8 +59,8 @@ def test_fc_parts_no_less_accurate_than_fp32(gpu, I):
         return np.linalg.norm(y - ref) / np.linalg.norm(ref)
 
     for cfg in _configs(gpu):
-        # 2^-25: the rounding of the result itself, which both have
-        assert err(cfg) <= err(0) + 2.0 ** -25
+        print(f"I {I} config {cfg}: {err(cfg) / err(0):.3f}", flush=True)
+        assert err(cfg) <= err(0)
 
 
 @pytest.mark.parametrize("xs,ws", [(-115, 0), (0, -120), (-140, 60), (-60, -70)])
@@ -90,3 +90,9 @@ def test_fc_parts_just_inside_the_range(gpu, sign):
         for cfg in [0] + _configs(gpu):
             got = to_host(gpu.cnn_fc_fwd(to_dev(x), to_dev(w), None, False, config=cfg))
             assert (np.abs(got - ref) <= live * 2.0 ** -23 * np.abs(ref)).all(), f"I {I} config {cfg}"
+
+
+def test_fc_of_one_input_stays_in_fp32(gpu):
+    """One product a sum: the fp32 value itself, which the parts miss by up to 3% more than its rounding."""
+    x, w = wl.normal((24, 1), 1.0, 64, 0), wl.normal((96, 1), 1.0, 64, 1)
+    np.testing.assert_array_equal(to_host(gpu.cnn_fc_fwd(to_dev(x), to_dev(w), None, False)), x * w.T)
