@@ -8,9 +8,8 @@ namespace {
 template <int FM, int FN, int KW>
 int launch_direct(const ConvParams& prm, bool vec_w, hipStream_t st) {
     const dim3 grid(ceil_div(prm.M, FN * 32), ceil_div(prm.Kg, FM * 32), prm.G * prm.splits), block(64 * KW);
-    const int niter = ceil_div(ceil_div(prm.kchunk, 16), KW);
     const int window = direct_window(prm);
-    const size_t shm = (size_t)(niter + kDirectStages) * KW * 16 * 4 * (window == kWindowAny ? 2 : 1);
+    const size_t shm = (size_t)direct_table_entries(prm.kchunk, KW) * 4 * (window == kWindowAny ? 2 : 1);
     if (shm > kDirectTableBytes) return fail(CNN_ERR_UNSUPPORTED, "conv: tap table of %zu bytes", shm);
 #define GO(V, M) enqueue((conv2d_direct_f32<FM, FN, KW, V, M>), grid, block, shm, st, prm)
     if (vec_w) {

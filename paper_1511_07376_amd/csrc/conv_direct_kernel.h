@@ -51,7 +51,7 @@ conv2d_direct_f32(ConvParams p) {
     // tap table, padded to a whole round of runs plus the runs in flight
     const int nrun = (klen + 15) / 16;
     const int niter = (nrun + KW - 1) / KW;  // runs per wave
-    const int ntab = (niter + D) * KW * 16;
+    const int ntab = direct_table_entries(p.kchunk, KW);
     for (int kk = threadIdx.x; kk < ntab; kk += NT) {
         const int c = (int)fdiv(kbeg + kk, p.f_rs);
         const int rs = kbeg + kk - c * p.RS;

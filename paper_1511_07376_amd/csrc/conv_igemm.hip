@@ -83,13 +83,12 @@ void choose_splits(ConvParams& p, const ConvConfig& c) {
     p.kchunk = k.kchunk;
 }
 
-// Whether a direct kernel's tap tables (two words a tap at most, the padding
-// of up to six rounds of the workgroup's waves included) fit the chunk, and the
-// filter and the image fit the packed rows and columns of kWindowAny: 15 and 16
+// Whether a direct kernel's tap tables (two words a tap at most) hold the chunk,
+// and the filter and the image fit the packed rows and columns of kWindowAny: 15 and 16
 // bits, and row 0x7fff, which marks "past the reduction", outside the image from
 // the first window on.
 __attribute__((always_inline)) inline bool direct_fits(const ConvParams& p, int kchunk, const ConvConfig& c) {
-    if (ceil_div(kchunk, 16) + 6 * (c.threads / 64) > kDirectTableBytes / (16 * 8)) return false;
+    if (kchunk > kDirectTableBytes / 8 || direct_table_entries(kchunk, c.threads / 64) > kDirectTableBytes / 8) return false;
     return direct_window(p) != kWindowAny || (p.R <= 0x7fff && p.S <= 0xffff && p.H <= 0x7fff - p.ph);
 }
 

@@ -625,9 +625,14 @@ int launch_cfg(const ConvParams& prm, bool vec_w, hipStream_t st) {
     X(23, 1, 1, 8)            \
     X(24, 1, 2, 4)
 constexpr int kDirectStages = 2;  // 16-tap runs of loads in flight per wave
-// LDS the tap tables of a direct kernel may take; reductions that need more
-// are split further across workgroups.
+// LDS the tap tables of a direct kernel may take; the 64 x 64 tiles take calls
+// that need more.
 constexpr int kDirectTableBytes = 64 * 1024;
+// Entries of a tap table: whole rounds of the workgroup's waves over the chunk's
+// 16-tap runs, and the runs in flight past them.
+__host__ __device__ inline int direct_table_entries(int kchunk, int waves) {
+    return ((kchunk + 16 * waves - 1) / (16 * waves) + kDirectStages) * waves * 16;
+}
 // Window tap tables (LDS, one entry per tap of the chunk):
 //  kWindowNoPad:   byte offset of the tap within an image group; no padding.
 //  kWindowMask:    (byte offset << 5) | (r*S + s), tap index 31 past the

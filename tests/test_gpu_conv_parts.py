@@ -32,15 +32,40 @@ def test_direct_every_run_count(gpu, taps):
 
 
 def test_direct_reduction_beyond_the_tap_tables(gpu):
-    """A 9216-tap reduction of 100 tiles does not fit the direct kernels' tap
-    tables: the call takes the tiled kernels instead."""
+    """A 9216-tap reduction of more than 64 tiles (so not split) does not fit the
+    direct kernels' tap tables: the call takes the tiled kernels instead."""
     x = wl.normal((16, 1024, 15, 15), 1.0, 41, 0)
-    w = wl.normal((30, 1024, 3, 3), 1.0, 41, 1)
+    w = wl.normal((60, 1024, 3, 3), 1.0, 41, 1)
     ref = oracle.conv2d_fwd(x[[0, 15]], w, None, (1, 1), (1, 1), 1, True)
     for cfg in _configs(gpu, "direct"):
         print(f"config {cfg}", flush=True)
         y = gpu.cnn_conv2d_fwd(to_dev(x), to_dev(w), None, 1, 1, 1, True, config=cfg)
         assert_gemm_close(y[[0, 15]].cpu().numpy(), ref, 9216, f"config {cfg}")
+
+
+@pytest.mark.parametrize("filter", [(1, 1, 0), (3, 3, 1), (7, 5, 2)], ids=["unpadded", "mask", "any"])
+def test_direct_largest_tap_tables(gpu, filter):
+    """The longest reductions that fit the tables, and the first that do not.
+    Which kernel ran shows in the sums: all products are 1 but two, 2^60 and
+    -2^60, which swallow the ones added between them.  They lie in the first two
+    16-tap runs of one wave of a direct kernel (32 taps, of which at most two
+    count), but 80 and 144 consecutive taps apart for the tiled kernels."""
+    R, S, pad = filter
+    table = 64 * 1024 // 8  # two words a tap
+    for cfg, waves in zip(_configs(gpu, "direct"), (4, 8, 4)):
+        longest = table - 2 * 16 * waves  # two rounds of runs are in flight
+        C = longest // (R * S)
+        for c, direct in ((C, True), (C + 1, False)):
+            taps = c * R * S
+            print(f"config {cfg} taps {taps}", flush=True)
+            x = torch.ones((1, c, 48, 48), device="cuda")
+            w = torch.ones((60, taps), device="cuda")
+            w[:, 0], w[:, 16 * waves + 15] = 2.0 ** 60, -2.0 ** 60
+            y = gpu.cnn_conv2d_fwd(x, w.reshape(60, c, R, S), None, 1, pad, 1, False, config=cfg)
+            inner = to_host(y[:, :, pad:y.shape[2] - pad, pad:y.shape[3] - pad])
+            gone = taps - inner
+            assert gone.min() == gone.max()
+            assert 30 <= gone.max() <= 32 if direct else 16 * waves <= gone.max() <= 16 * waves + 16
 
 
 @pytest.mark.parametrize("shape", [
