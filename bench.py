@@ -29,6 +29,8 @@ sys.path.insert(0, ROOT)
 
 METRIC = "images/sec + conv GFLOP/s (% fp32 MFMA peak), AlexNet-shaped fp32 batch 64"
 PEAK_FP32_MFMA_TFLOPS = 157.3   # MI355X dense fp32 matrix peak
+PEAK_BF16_MFMA_TFLOPS = 2500.0  # MI355X dense bf16 matrix peak
+PARTS_PRODUCTS = 6              # bf16 products per fp32 product of the configurations on bf16 parts
 PEAK_HBM_GBS = 8000.0           # MI355X HBM3E
 
 # HIP runtime setting for the timed process: kernel arguments in device memory
@@ -124,6 +126,17 @@ def conv_configs_of(tuning_text, layer):
         if (v[1], v[4], v[5], v[6], v[7], v[8], v[11]) == want:
             cfgs.append(v[12])
     return sorted(cfgs)
+
+
+def matrix_roof(kind, config_names):
+    """Matrix-core peak (TFLOP/s of the layer's own operations) a conv or FC
+    layer is held against, and what sets it: the fp32 instructions' peak, or for
+    convolutions on bf16 parts the bf16 peak over the products of parts.
+    config_names: the tuned configurations' names; without one (the built-in
+    choice may take either) a convolution is held against the higher peak."""
+    if kind == "conv" and (not config_names or any(n.startswith("bf16 parts") for n in config_names)):
+        return PEAK_BF16_MFMA_TFLOPS / PARTS_PRODUCTS, f"bf16 matrix cores, {PARTS_PRODUCTS} products of parts"
+    return PEAK_FP32_MFMA_TFLOPS, "fp32 matrix cores"
 
 
 def stored_traffic(workload, layer_name, layer=None, tuning_text=None, prof_dir=None):
@@ -753,18 +766,20 @@ def main():
     dom = int(np.argmax(layer_ms))
     dname, dkind, dflops, dbytes = work[dom]
     workload = f"{net.name}_b{batch}"
-    if dkind in ("conv", "fc"):
-        ach = dflops / (layer_ms[dom] * 1e-3) / 1e12
-        roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": PEAK_FP32_MFMA_TFLOPS,
-                "unit": "TFLOP/s", "frac": round(ach / PEAK_FP32_MFMA_TFLOPS, 4)}
-    else:
-        ach = dbytes / (layer_ms[dom] * 1e-3) / 1e9
-        roof = {"bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
-                "frac": round(ach / PEAK_HBM_GBS, 4)}
     named, counts = {}, {}
     for layer in net.layers:  # the names layer_work gives
         counts[layer.kind] = counts.get(layer.kind, 0) + 1
         named[f"{layer.kind}{counts[layer.kind]}"] = layer
+    if dkind in ("conv", "fc"):
+        ach = dflops / (layer_ms[dom] * 1e-3) / 1e12
+        tuned = conv_configs_of(cnn.cnn_tuning_export(), named[dname]) if dkind == "conv" else []
+        peak, on = matrix_roof(dkind, [cnn.cnn_conv2d_config_name(c) for c in tuned])
+        roof = {"bound": "mfma", "achieved": round(ach, 2), "peak": round(peak, 1),
+                "unit": "TFLOP/s", "frac": round(ach / peak, 4), "peak_of": on}
+    else:
+        ach = dbytes / (layer_ms[dom] * 1e-3) / 1e9
+        roof = {"bound": "hbm", "achieved": round(ach, 1), "peak": PEAK_HBM_GBS, "unit": "GB/s",
+                "frac": round(ach / PEAK_HBM_GBS, 4)}
     roof["traffic"] = stored_traffic(workload, dname, named.get(dname), cnn.cnn_tuning_export())
     roof["layer"] = dname
     roof["launch_ms"] = round(layer_ms[dom], 5)

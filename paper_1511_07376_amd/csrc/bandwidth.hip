@@ -237,8 +237,7 @@ __global__ void __launch_bounds__(kThreads) avgpool_f32(PoolParams p) {
 // it; the pixels it shares are written twice, with the same values), and the
 // chunks of the same pixels are neighbouring waves, so that the halo comes from
 // the caches.  64 x 96 x 55 x 55, five channels: 36.4 us with one pixel and 32
-// channels a lane, 33.8 with four and 8 (9 waves a SIMD in flight against 3),
-// 26.2 with non-temporal stores on top (a plain copy of it: 26.9); 12 and 16
+// channels a lane, 33.8 with four and 8, 26.2 with non-temporal stores on top (a plain copy of it: 26.9); 12 and 16
 // channels 26.0 and 27.5 there, but 19.2 and 19.6 against 17.0 on 64 x 256 x 27
 // x 27.
 struct LrnParams {

@@ -179,11 +179,14 @@ __device__ inline void store_blocks(const ConvParams& p, const floatx16 (&acc)[F
     }
 }
 
-// ST: register stages (slabs of loads in flight).  The compiler is held to the
-// waves per SIMD that the accumulators of a wave's tile leave room for.
+// ST: register stages (slabs of loads in flight).  The compiler is held to two
+// or three waves per SIMD: one step of fragments, two sets of accumulators, the
+// stages and the parts in flight take 100 to 256 registers a lane, within the
+// limit but for configuration 18 with vector weight loads and a tap table (24 to
+// 28 bytes of scratch).
 template <int WMW, int WNW, int FM, int FN, int BK, bool VEC_W, int GATHER, int ST>
 __global__ void __launch_bounds__(64 * WMW * WNW)
-__attribute__((amdgpu_waves_per_eu(FM * FN >= 6 ? 1 : FM * FN >= 3 || BK == 32 ? 2 : 3)))
+__attribute__((amdgpu_waves_per_eu(FM * FN >= 3 || BK == 32 ? 2 : 3)))
 conv2d_split_f32(ConvParams p) {
     static_assert(ST % 2 == 0, "the two LDS buffers alternate within a round of ST slabs");
     constexpr int TM = WMW * FM * 32;  // output channels per workgroup
@@ -600,19 +603,20 @@ int launch_split(const ConvParams& prm, bool vec_w, hipStream_t st) {
     else if (tab_fits && prm.RS <= 31 && (int64_t)prm.Cg * prm.HW * 4 < ((int64_t)1 << 27))
         mode = kGatherMask;
     const size_t shm = mode == kGatherScalar ? 0 : (size_t)tab_entries * 4;
-    if (vec_w) {
-        if (mode == kGatherStridedMask) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherStridedMask>(prm, grid, block, shm, st);
-        else if (mode == kGatherStrided) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherStrided>(prm, grid, block, shm, st);
-        else if (mode == kGatherNoPad) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherNoPad>(prm, grid, block, shm, st);
-        else if (mode == kGatherMask) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherMask>(prm, grid, block, shm, st);
-        else launch_split_kernel<WMW, WNW, FM, FN, BK, ST, true, kGatherScalar>(prm, grid, block, shm, st);
+    // the strided gathers load weights tap by tap whatever the rows' alignment
+#define GO(V, M) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, V, M>(prm, grid, block, shm, st)
+    if (mode == kGatherStridedMask) GO(false, kGatherStridedMask);
+    else if (mode == kGatherStrided) GO(false, kGatherStrided);
+    else if (vec_w) {
+        if (mode == kGatherNoPad) GO(true, kGatherNoPad);
+        else if (mode == kGatherMask) GO(true, kGatherMask);
+        else GO(true, kGatherScalar);
     } else {
-        if (mode == kGatherStridedMask) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherStridedMask>(prm, grid, block, shm, st);
-        else if (mode == kGatherStrided) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherStrided>(prm, grid, block, shm, st);
-        else if (mode == kGatherNoPad) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherNoPad>(prm, grid, block, shm, st);
-        else if (mode == kGatherMask) launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherMask>(prm, grid, block, shm, st);
-        else launch_split_kernel<WMW, WNW, FM, FN, BK, ST, false, kGatherScalar>(prm, grid, block, shm, st);
+        if (mode == kGatherNoPad) GO(false, kGatherNoPad);
+        else if (mode == kGatherMask) GO(false, kGatherMask);
+        else GO(false, kGatherScalar);
     }
+#undef GO
     return check_launch("conv2d_split_f32");
 }
 

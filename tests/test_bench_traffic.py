@@ -71,3 +71,14 @@ def test_committed_records_carry_their_tuning_table():
                 rec = json.load(f)
             assert rec.get("tuning"), name
             assert all(len(line.split()) == 13 for line in rec["tuning"]), name
+
+
+def test_roofline_peak_follows_the_kernel():
+    """A convolution on bf16 parts is held against the bf16 peak over its six
+    products of parts (the fp32 peak gave fractions above 1)."""
+    fp32 = "2x2 waves, 2x2 blocks, BK 16, 1 slab groups"
+    parts = "bf16 parts, 2x2 waves, 2x2 blocks, BK 16"
+    assert bench.matrix_roof("conv", [fp32])[0] == bench.matrix_roof("fc", [])[0] == 157.3
+    assert bench.matrix_roof("conv", ["direct, 1x1 blocks, 4 waves"])[0] == 157.3
+    assert abs(bench.matrix_roof("conv", [parts])[0] - 2500 / 6) < 1e-9
+    assert abs(bench.matrix_roof("conv", [])[0] - 2500 / 6) < 1e-9
