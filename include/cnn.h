@@ -88,7 +88,12 @@ const char* cnn_conv2d_config_name(int i);
 
 /* cnn_conv2d_fwd with an explicit tile configuration: 0 <= config <
  * cnn_conv2d_num_configs(), or -1 for the built-in heuristic (ignoring any
- * tuned entry).  Every configuration computes the same function. */
+ * tuned entry).  Every configuration computes the same function, with sums in
+ * fp32: on the fp32 matrix cores, or on the bf16 ones from operands split
+ * exactly into three parts (sums with an operand that does not split, some
+ * below 2^-107, and sums that come out infinite or NaN are computed again on
+ * the fp32 ones).  A direct configuration whose tap tables cannot hold the
+ * filter and its reduction runs as one of 64 x 64 tiles. */
 int cnn_conv2d_fwd_config(const float* x, int N, int C, int H, int W,
                           const float* w, int K, int R, int S, const float* bias,
                           int sh, int sw, int ph, int pw, int groups, int fuse_relu,
@@ -98,8 +103,9 @@ int cnn_conv2d_fwd_config(const float* x, int N, int C, int H, int W,
  * cnn_conv2d_fwd / cnn_net_fwd call that meets a new convolution shape runs
  * every configuration on that call's own buffers, synchronising its stream
  * (not while the stream is being captured), and records the fastest for the
- * shape; the call then returns normally with the result of the chosen
- * configuration.  Later calls of the shape use the record, tuning on or off. */
+ * shape (inside a network without the fill and the ReLU of split reductions,
+ * which other layers' kernels do there); the call then returns normally with
+ * the result of the chosen configuration.  Later calls of the shape use the record, tuning on or off. */
 int cnn_set_autotune(int mode);
 
 /* The tuning records as text, one line per shape:

@@ -126,8 +126,10 @@ ConvPlan conv2d_plan(const ConvShape& s, int cfg);
 // (cnn_conv2d_fwd_config runs another where a direct kernel's tables are too
 // small) and gives up no accuracy.
 bool conv2d_config_takes(const ConvShape& s, int c);
-// The built-in heuristic's configuration for this shape (-1 if none applies).
-int conv2d_heuristic_config(const ConvShape& s);
+// The built-in heuristic's configuration for this shape (-1 if none applies);
+// in_net: for a layer of a network, whose split reductions are filled and
+// rectified by other layers' kernels.
+int conv2d_heuristic_config(const ConvShape& s, bool in_net);
 // Convolution with the tuned configuration for this shape (auto-tuning it
 // first when auto-tuning is on and the shape is new).
 int conv2d_dispatch(const ConvShape& s, const float* x, const float* w, const float* bias,

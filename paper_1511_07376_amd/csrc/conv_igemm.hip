@@ -115,6 +115,13 @@ constexpr TimeModel kFp32Model = {5.62, 0.464, 1.08, 0.243, 7.14, 1.12},
                     kDirectModel = {4.75, 0.303, 1.04, 0.34, 3.63, 4.54};
 // A call's least time: one launch, or those of a split reduction.
 constexpr double kLeastUs = 8.4, kLeastSplitUs = 14.0;
+// A layer of a network has neither that nor launches for the fill and the ReLU
+// of a split reduction, which other layers' kernels do.  What is left of them,
+// from passes of AlexNet, LeNet and CIFAR-10 quick at 19 batch sizes with 0 to 8
+// us: with 1.5 AlexNet's at 1, 4 and 16 images takes 115.8, 182.1 and 326.5 us
+// and CIFAR-10 quick's at 1 and 8 images 32.8 and 35.4; with a standalone call's
+// estimates 122.1, 177.3, 332.2, 41.3 and 44.8.
+constexpr double kFillInNetUs = 1.5;
 // Per slab of one workgroup (us): latency alone, throughput share; scales of
 // the two for strided gathers; of both for the other ways to read operands.
 struct SlabTime {
@@ -150,7 +157,7 @@ constexpr SlabTime slab_time(int cfg) {
 // its divisions become shifts, and the ten take 95 ns (470 with a loop over the
 // table).
 template <int CFG>
-double estimate(const ConvParams& p, const Chunks& k) {
+double estimate(const ConvParams& p, const Chunks& k, bool in_net) {
     constexpr ConvConfig c = kConfigs[CFG];
     constexpr TimeModel f = c.direct ? kDirectModel : CFG >= kFirstSplit ? kSplitModel : kFp32Model;
     constexpr SlabTime t = slab_time(CFG);
@@ -168,17 +175,19 @@ double estimate(const ConvParams& p, const Chunks& k) {
                                  queue * t.share * (strided ? t.strided_share : 1.0)) * scale;
     const double mout = 1e-6 * ((double)p.M * p.K);
     const double us = f.base + (slabs + f.extra) * slab + 4.0 * f.out * mout;
-    return k.splits > 1 ? std::max(kLeastSplitUs, us + f.fill + f.sums * k.splits * mout) : std::max(kLeastUs, us);
+    const double sums = k.splits > 1 ? f.sums * k.splits * mout : 0.0;
+    if (in_net) return us + sums + (k.splits > 1 ? kFillInNetUs : 0.0);
+    return k.splits > 1 ? std::max(kLeastSplitUs, us + f.fill + sums) : std::max(kLeastUs, us);
 }
-double estimate_fp32(const ConvParams& p, int cfg) {
+double estimate_fp32(const ConvParams& p, int cfg, bool in_net) {
     switch (cfg) {  // every choice of fp32_config
-        case 0: return estimate<0>(p, chunks_of(p, kConfigs[0]));
-        case 2: return estimate<2>(p, chunks_of(p, kConfigs[2]));
-        case 4: return estimate<4>(p, chunks_of(p, kConfigs[4]));
-        case 6: return estimate<6>(p, chunks_of(p, kConfigs[6]));
-        case 8: return estimate<8>(p, chunks_of(p, kConfigs[8]));
-        case 9: return estimate<9>(p, chunks_of(p, kConfigs[9]));
-        default: return estimate<10>(p, chunks_of(p, kConfigs[10]));
+        case 0: return estimate<0>(p, chunks_of(p, kConfigs[0]), in_net);
+        case 2: return estimate<2>(p, chunks_of(p, kConfigs[2]), in_net);
+        case 4: return estimate<4>(p, chunks_of(p, kConfigs[4]), in_net);
+        case 6: return estimate<6>(p, chunks_of(p, kConfigs[6]), in_net);
+        case 8: return estimate<8>(p, chunks_of(p, kConfigs[8]), in_net);
+        case 9: return estimate<9>(p, chunks_of(p, kConfigs[9]), in_net);
+        default: return estimate<10>(p, chunks_of(p, kConfigs[10]), in_net);
     }
 }
 
@@ -199,23 +208,23 @@ constexpr int kLeastSplitTaps = 2;
 constexpr double kMargin = 1.06, kMarginManyWorkgroups = 1.01;
 constexpr double kMarginSplitOrDirect = 1.05;  // on top of it, for a split reduction or a direct kernel
 template <int CFG>
-__attribute__((always_inline)) inline void consider(const ConvParams& p, int* best, double* least) {
+__attribute__((always_inline)) inline void consider(const ConvParams& p, bool in_net, int* best, double* least) {
     constexpr ConvConfig c = kConfigs[CFG];
     const Chunks k = chunks_of(p, c);
     if (c.direct ? !direct_fits(p, k.kchunk, c) : p.Kr < kLeastSplitTaps) return;
     const int64_t wgs = (int64_t)ceil_div(p.M, c.tn) * ceil_div(p.Kg, c.tm) * p.G * k.splits;
-    double us = estimate<CFG>(p, k) * (wgs > 5 * 256 ? kMarginManyWorkgroups : kMargin);
+    double us = estimate<CFG>(p, k, in_net) * (wgs > 5 * 256 ? kMarginManyWorkgroups : kMargin);
     if (c.direct || k.splits > 1) us *= kMarginSplitOrDirect;
     if (us < *least) {
         *least = us;
         *best = CFG;
     }
 }
-int heuristic_config(const ConvParams& p, int G) {
+int heuristic_config(const ConvParams& p, int G, bool in_net) {
     int best = fp32_config(p, G);
-    double least = estimate_fp32(p, best);
-    if (least <= kLeastUs) return best;  // no other is estimated below kLeastUs
-#define CNN_CONSIDER(I, ...) consider<I>(p, &best, &least);
+    double least = estimate_fp32(p, best, in_net);
+    if (!in_net && least <= kLeastUs) return best;  // no other is estimated below kLeastUs
+#define CNN_CONSIDER(I, ...) consider<I>(p, in_net, &best, &least);
     CNN_SPLIT_CONFIGS(CNN_CONSIDER)
     CNN_DIRECT_CONFIGS(CNN_CONSIDER)
 #undef CNN_CONSIDER
@@ -239,8 +248,9 @@ namespace {
 
 // Parameters, configuration and reduction split of a convolution; per_launch:
 // images per launch (the gather's 31-bit offsets cover fewer than 2^29 input
-// elements).  cfg < 0 on entry: the heuristic's choice.
-int conv_prepare(const ConvShape& s, int* cfg, ConvParams* out, int* per_launch) {
+// elements).  cfg < 0 on entry: the heuristic's choice, for a layer of a network
+// or for a call by itself.
+int conv_prepare(const ConvShape& s, int* cfg, ConvParams* out, int* per_launch, bool in_net = false) {
     ConvParams& prm = *out;
     prm.C = s.C; prm.H = s.H; prm.W = s.W; prm.K = s.K; prm.R = s.R; prm.S = s.S;
     prm.P = s.P; prm.Q = s.Q;
@@ -266,7 +276,7 @@ int conv_prepare(const ConvShape& s, int* cfg, ConvParams* out, int* per_launch)
     *per_launch = (int)std::min<int64_t>(std::max(s.N, 1), (((int64_t)1 << 29) - 1) / img);
     if (*per_launch < 1) return fail(CNN_ERR_UNSUPPORTED, "conv: one image exceeds 2^29 elements");
     prm.M = *per_launch * prm.PQ;
-    if (*cfg < 0) *cfg = heuristic_config(prm, s.G);
+    if (*cfg < 0) *cfg = heuristic_config(prm, s.G, in_net);
     if (*cfg >= kNumConfigs) return fail(CNN_ERR_UNSUPPORTED, "conv: no configuration %d", *cfg);
     // One split decision for every launch of the call (the last one may hold
     // fewer images: splitting it the same way is still correct).
@@ -287,17 +297,17 @@ bool conv2d_config_takes(const ConvShape& s, int c) {
     return kConfigs[c].direct || c < conv::kFirstSplit || prm.Kr >= conv::kLeastSplitTaps;
 }
 
-int conv2d_heuristic_config(const ConvShape& s) {
+int conv2d_heuristic_config(const ConvShape& s, bool in_net) {
     ConvParams prm;
     int per_launch, cfg = -1;
-    return conv_prepare(s, &cfg, &prm, &per_launch) == CNN_OK ? cfg : -1;
+    return conv_prepare(s, &cfg, &prm, &per_launch, in_net) == CNN_OK ? cfg : -1;
 }
 
 ConvPlan conv2d_plan(const ConvShape& s, int cfg) {
     ConvPlan plan = {false, false, -1};
     ConvParams prm;
     int per_launch, used = cfg == -2 ? 0 : cfg;
-    if (conv_prepare(s, &used, &prm, &per_launch) != CNN_OK) return plan;
+    if (conv_prepare(s, &used, &prm, &per_launch, true) != CNN_OK) return plan;
     plan.split = cfg != -2 && prm.splits > 1;
     if (cfg == -1) plan.heuristic = used;
     plan.may_split = plan.split;
@@ -311,7 +321,7 @@ int launch_conv2d(const ConvShape& s, const float* x, const float* w, const floa
     if (s.N == 0) return CNN_OK;
     ConvParams prm;
     int per_launch;
-    int rc = conv_prepare(s, &cfg, &prm, &per_launch);
+    int rc = conv_prepare(s, &cfg, &prm, &per_launch, opt != nullptr);
     if (rc != CNN_OK) return rc;
     prm.w = w;
     prm.bias = bias;

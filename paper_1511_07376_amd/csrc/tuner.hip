@@ -50,8 +50,10 @@ constexpr float kHeuristicMargin = 0.02f;
 // Configurations a few percent apart can swap places from one timing to the
 // next, so the fastest few of the first pass are timed again, interleaved,
 // and each keeps its best round.
+// in_net: a layer of a network, whose split reductions are filled and rectified
+// by other layers' kernels; the candidates run without either then.
 int tune(const ConvShape& s, const float* x, const float* w, const float* bias, int relu, float* y,
-         hipStream_t st) {
+         hipStream_t st, bool in_net) {
     hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
     if (hipStreamIsCapturing(st, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) return -1;
     hipEvent_t e0, e1;
@@ -60,12 +62,17 @@ int tune(const ConvShape& s, const float* x, const float* w, const float* bias, 
         (void)hipEventDestroy(e0);
         return -1;
     }
+    bool relu_left;
+    ConvOpts as_layer;
+    as_layer.prefilled = true;
+    as_layer.relu_left = &relu_left;
+    const ConvOpts* opt = in_net ? &as_layer : nullptr;
     // ms per run of configuration c over `runs` back-to-back launches; < 0 on failure
     auto time_cfg = [&](int c, int runs) -> float {
-        if (launch_conv2d(s, x, w, bias, relu, y, st, c) != CNN_OK) return -1.0f;  // warm-up run
+        if (launch_conv2d(s, x, w, bias, relu, y, st, c, opt) != CNN_OK) return -1.0f;  // warm-up run
         if (hipEventRecord(e0, st) != hipSuccess) return -1.0f;
         for (int r = 0; r < runs; ++r)
-            if (launch_conv2d(s, x, w, bias, relu, y, st, c) != CNN_OK) return -1.0f;
+            if (launch_conv2d(s, x, w, bias, relu, y, st, c, opt) != CNN_OK) return -1.0f;
         if (hipEventRecord(e1, st) != hipSuccess) return -1.0f;
         if (hipEventSynchronize(e1) != hipSuccess) return -1.0f;
         float ms = 0.0f;
@@ -80,7 +87,7 @@ int tune(const ConvShape& s, const float* x, const float* w, const float* bias, 
     }
     std::sort(first.begin(), first.end());
     int nf = std::min<int>(kFinalists, (int)first.size());
-    const int heur = conv2d_heuristic_config(s);
+    const int heur = conv2d_heuristic_config(s, in_net);
     int heur_at = -1;  // the heuristic's place among the finalists (it joins them)
     for (int i = 0; i < (int)first.size(); ++i)
         if (first[i].second == heur) {
@@ -134,7 +141,7 @@ int conv2d_dispatch(const ConvShape& s, const float* x, const float* w, const fl
     if (cfg < 0 && autotune && s.N > 0 && !(opt && opt->no_tune)) {
         {
             SpanPause pause;  // the candidates' runs are not the layer's
-            cfg = tune(s, x, w, bias, relu, y, st);
+            cfg = tune(s, x, w, bias, relu, y, st, opt != nullptr);
         }
         if (cfg >= 0) {
             std::lock_guard<std::mutex> lock(g_mu);

@@ -8,11 +8,11 @@ from paper_1511_07376_amd import cnn
 FIRST_SPLIT, FIRST_DIRECT = 16, 22  # configurations below take the fp32 tiles
 
 
-def choice(n, c, h, w, k, r, s, stride, pad, groups):
+def choice(n, c, h, w, k, r, s, stride, pad, groups, in_net=False):
     """conv2d_heuristic_config of the shape."""
     p, q = cnn.cnn_conv2d_out_shape(h, w, r, s, stride, pad)
     shape = (ctypes.c_int * 14)(n, c, h, w, k, r, s, stride, stride, pad, pad, groups, p, q)
-    return cnn.lib._ZN3cnn23conv2d_heuristic_configERKNS_9ConvShapeE(ctypes.byref(shape))
+    return cnn.lib._ZN3cnn23conv2d_heuristic_configERKNS_9ConvShapeEb(ctypes.byref(shape), in_net)
 
 
 # N, C, H, W, K, R, S, stride, pad, groups; us on the fp32 choice, and on the
@@ -62,3 +62,13 @@ def test_sums_of_one_tap_stay_in_fp32(n):
     # a reduction beyond the direct kernels' tap tables is not tuned under their names
     long = (ctypes.c_int * 14)(16, 1024, 15, 15, 60, 3, 3, 1, 1, 1, 1, 1, 15, 15)
     assert [takes(ctypes.byref(long), cfg) for cfg in range(FIRST_DIRECT, cnn.cnn_conv2d_num_configs())] == [False] * 3
+
+
+@pytest.mark.parametrize("shape", [
+    (16, 256, 15, 15, 384, 3, 3, 1, 0, 1),  # AlexNet's conv3 at batch 16
+    (1, 256, 15, 15, 384, 3, 3, 1, 0, 1),   # ... on one image
+], ids=["b16", "b1"])
+def test_split_reductions_are_cheaper_inside_a_network(shape):
+    """Their fill and ReLU cost a standalone call two launches, a network none."""
+    assert choice(*shape) >= FIRST_DIRECT
+    assert choice(*shape, in_net=True) < FIRST_SPLIT
