@@ -498,7 +498,7 @@ int run_net(const cnn_layer_desc* L, int n, const float* x, int N, int C, int H,
             }
             case CNN_LAYER_LRN:
                 rc = launch_lrn(cur, N, p.inC, p.inH, p.inW, d.lrn_size, d.lrn_alpha, d.lrn_beta,
-                                d.lrn_k, out, st, relu_in);
+                                d.lrn_k, out, st, relu_in, true);
                 break;
             case CNN_LAYER_RELU:
                 rc = launch_relu(cur, out, (int64_t)N * p.inC * p.inH * p.inW, st);

@@ -328,9 +328,16 @@ __global__ void __launch_bounds__(kThreads) lrn_across_f32(LrnParams p) {
     }
 }
 
-// nt: an output larger than the eight 4 MiB L2s together, which nothing that
-// follows finds there, is stored past them (16 x 96 x 55 x 55, 18 MB: 8.73 us
-// with plain stores, 8.84 past L2; 74 MB: 33.8 and 26.2).
+// nt: an output larger than the eight 4 MiB L2s together is stored past them
+// (from buffers that rotate through 700 MB, plain stores and past L2: 36 MB 19.3
+// and 16.8 us, 74 MB 33.6 and 30.0, 149 MB 62.7 and 57.5; 18 MB repeated 8.73 and
+// 8.84).  It passes the memory-side cache (256 MiB) by as well, which a network's
+// next layer would read it from, so there the line is where input and output
+// together outgrow that one (a 1x1 convolution before and after it: 36 MB 49.1
+// and 50.2 us for the three, 74 MB 84.9 and 87.9, 112 MB 132.4 and 135.5, 149 MB
+// 199.5 and 176.3; with a pooling after it 38.9 and 40.2, 67.4 and 68.3, 106.5
+// and 97.1, 149.7 and 139.2).
+constexpr int64_t kL2Bytes = (int64_t)8 * (4 << 20), kMallBytes = (int64_t)256 << 20;
 template <int HALF>
 void enqueue_lrn(const LrnParams& p, bool vec, bool nt, hipStream_t st) {
     constexpr int kChunk = 8;
@@ -633,7 +640,7 @@ int launch_pool(const PoolShape& s, int mode, int relu, const float* x, float* y
 }
 
 int launch_lrn(const float* x, int N, int C, int H, int W, int size, float alpha, float beta,
-               float k, float* y, hipStream_t st, bool relu_x) {
+               float k, float* y, hipStream_t st, bool relu_x, bool in_net) {
     LrnParams p;
     p.relu_x = relu_x;
     p.x = x;
@@ -655,7 +662,8 @@ int launch_lrn(const float* x, int N, int C, int H, int W, int size, float alpha
     // The chunked kernel addresses x through a buffer resource with 31-bit
     // byte offsets: fewer than 2^29 elements per launch (whole images).
     const int per_launch = (int)std::min<int64_t>(N, (((int64_t)1 << 29) - 1) / img);
-    const bool vec = p.HW >= 4, nt = N * img * 4 > (int64_t)8 * (4 << 20);
+    const int64_t bytes = N * img * 4;
+    const bool vec = p.HW >= 4, nt = bytes > (in_net ? kMallBytes / 2 : kL2Bytes);
     const int groups = vec ? ceil_div(p.HW, 4) : p.HW;  // of pixels in a plane
     p.f_pg = make_fastdiv(groups);
     for (int n0 = 0; n0 < N; n0 += per_launch) {

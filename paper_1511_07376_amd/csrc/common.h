@@ -189,8 +189,10 @@ using FillJobs = FillJobsOf<kMaxPoolFills>;
 // fills: bias fills the kernel also performs (NULL: none).
 int launch_pool(const PoolShape& s, int mode, int relu, const float* x, float* y, int32_t* idx,
                 hipStream_t st, bool relu_x = false, const FillJobs* fills = nullptr);
+// in_net: a layer of a network, whose output the next one reads at once.
 int launch_lrn(const float* x, int N, int C, int H, int W, int size, float alpha, float beta,
-               float k, float* y, hipStream_t st, bool relu_x = false);
+               float k, float* y, hipStream_t st, bool relu_x = false,
+               bool in_net = false);
 int launch_relu(const float* x, float* y, int64_t n, hipStream_t st);
 // LRN (across channels, odd size) followed by pooling of its output, in one
 // kernel; s is the pooling shape (its input is the LRN's shape).  Only where

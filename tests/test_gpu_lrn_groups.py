@@ -2,6 +2,7 @@
 below one group, and on outputs stored past L2."""
 import numpy as np
 import pytest
+import torch
 
 import oracle
 from conftest import to_dev, to_host
@@ -29,3 +30,14 @@ def test_lrn_output_larger_than_l2(gpu):
     y = gpu.cnn_lrn_fwd(x, 5)
     for n in (0, 15, 30):
         np.testing.assert_array_equal(to_host(y[n:n + 1]), to_host(gpu.cnn_lrn_fwd(x[n:n + 1].contiguous(), 5)))
+
+
+@pytest.mark.parametrize("batch", [2, 31, 116])
+def test_lrn_in_a_network_gives_the_same_values(gpu, batch):
+    """1, 37 and 140 MB: a network's line between the kinds of stores (input and
+    output together 256 MiB) lies elsewhere than a standalone call's."""
+    net = wl.Net(name="lrn", input_chw=(96, 55, 57), layers=(wl.lrn(5),), weight_std=0.0, bias_std=0.0,
+                 default_batch=batch, batches=(batch,))
+    x = torch.rand((batch, 96, 55, 57), device="cuda") * 20
+    y = gpu.Network(net, [None])(x)
+    assert torch.equal(y, gpu.cnn_lrn_fwd(x, 5))
