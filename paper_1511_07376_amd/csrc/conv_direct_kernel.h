@@ -8,7 +8,8 @@
 // partial tiles are summed through LDS in wave order.  So a layer whose whole
 // output is a hundred tiles runs on several waves per SIMD in one launch, with
 // no barrier in the reduction loop and no atomics, where the tiled kernels
-// need a bias fill, a split reduction and a ReLU pass.
+// need a bias fill, a split reduction and a ReLU pass.  (Layers of at most 64
+// tiles and long reductions are split here as well.)
 //
 // What bounds it is the latency of a run's loads (few runs a wave) and then
 // the texture addresser: a block's operands are loaded by every wave that

@@ -2,8 +2,7 @@
 //
 // An fp32 value is the exact sum of three bf16 parts (bf16_split.h; 24
 // significant bits in three times 8, each part's rounding error passed on to
-// the next).  A product of two values is
-// then nine products of parts, of which the three below 2^-24 of the whole are
+// the next).  A product of two values is then nine products of parts, of which the three below 2^-24 of the whole are
 // left out, and a v_mfma_f32_32x32x16_bf16 multiplies 16 taps in the time in
 // which the fp32 matrix instruction multiplies one (32 against 64 cycles for
 // 16 against 2 taps): six of them cost 3/8 of the fp32 time.
@@ -13,8 +12,8 @@
 // end.  Against 64-bit sums the error is 0.3 to 0.9 of the fp32 matrix
 // instruction's chain for 2 to 4608 taps of random values, signed or not
 // (1200 taps: 0.4 to 0.8; a single tap: 1.02 to 1.03, for the products left
-// out).  With one accumulator,
-// or with truncated parts, it is larger than the chain's for some signs.
+// out, which is why the choice and the tuner leave such sums to the fp32
+// kernels).  With one accumulator, or with truncated parts, it is larger than the chain's for some signs.
 //
 // What the parts cannot do is done again on the fp32 matrix cores, by the
 // waves whose sums it concerns (fp32_sums):
@@ -29,12 +28,14 @@
 //
 // The split is done once per loaded element, as it is stored to LDS, in steps
 // of a few vector instructions between the matrix-core instructions of the
-// slab before it.  What bounds it: the matrix cores at 54% of busy cycles, the
-// rest barriers and LDS latency between slabs, at a clock that bf16 matrix
-// work on random data holds at 2.1 GHz (a loop of nothing but these
-// instructions reaches 1.8 of the nominal 2.5 PFLOP/s).  256x28x28 -> 256,
-// 3x3, 64 images: 505 -> 412 us (144 TFLOP/s of the layer's own operations);
-// AlexNet at batch 64: 861 -> 723 us.
+// slab before it.  What bounds it: the matrix cores are busy 41 to 44% of the
+// cycles, 49 to 51% of those in which the compute unit is (256x28x28 -> 256,
+// 3x3, 64 images, and AlexNet's conv2; rocprofv3 counters), the rest is barriers
+// and LDS latency between slabs, at a clock that bf16 matrix work on random
+// data holds at 2.1 GHz (a loop of nothing but these instructions reaches 1.8
+// of the nominal 2.5 PFLOP/s).  On 256x28x28 -> 256, 3x3, 64 images: 505 -> 391
+// to 402 us (147 to 151 TFLOP/s of the layer's own operations);
+// AlexNet at batch 64: 859 -> 738 us on one box, 865 -> 767 on another.
 #pragma once
 
 #include <cstring>

@@ -821,9 +821,11 @@ constexpr int kNumFcConfigs = sizeof(kFcConfigs) / sizeof(kFcConfigs[0]);
 // in three.  Over 22 shapes of 3 to 256 images, 64 to 1000 features in and 10
 // to 4096 out: 3.7 to 11.1 us against 5.1 to 18 (610 -> 188 at 230 images 14.1
 // -> 8.1, 512 -> 4096 at 64 13.3 -> 11.1; 512 -> 512 at 200 10.7 -> 10.9).  The
-// fp32 direct kernel's shapes stay with it: by themselves 800 -> 500 at 16
-// images took 9.0 against 7.6 us, but in LeNet, where the fill and the ReLU
-// cost it nothing, the network ran 3 us faster with it.  Longer reductions are
+// fp32 direct kernel's shapes stay with it for the networks' sake: in LeNet, where
+// its fill and ReLU cost nothing, the network ran 3 us faster with it than on
+// parts.  A call by itself pays two launches for them: 800 -> 500 at 16 images
+// 14.6 against 9.0 us on parts, 500 -> 10 15.1 and 8.7, 412 -> 540 at 7 images
+// 14.1 and 8.5.  Longer reductions are
 // bound by the 32-row loads (1024 -> 64 at 64 images 10.0 -> 16.0, 9216 -> 4096
 // 54 -> 80 split), except for at most 32 images with rows that are not whole
 // 16-byte vectors, which leave the tiled kernels 32-bit loads: split, 2600 to
